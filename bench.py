@@ -42,16 +42,17 @@ _CSRC = os.path.join(ROOT, "paper_2206_01683_amd", "csrc")
 # the sources each main kernel is compiled from, and its committed HBM traffic summary
 KERNEL_SOURCES = {
     "k_collide": [os.path.join(_CSRC, f) for f in ("lattice.hpp", "env.hpp", "fluid.hpp")],
-    "k_step_overlap": [os.path.join(_CSRC, f) for f in ("lattice.hpp", "env.hpp", "fluid.hpp", "ib.hpp", "step.hpp")],
+    "k_step": [os.path.join(_CSRC, f) for f in ("lattice.hpp", "env.hpp", "fluid.hpp", "ib.hpp", "step.hpp")],
 }
 TRAFFIC_FILES = {
     "k_collide": os.path.join(ROOT, "profiles", "collide_traffic.txt"),
-    "k_step_overlap": os.path.join(ROOT, "profiles", "step_overlap_traffic.txt"),
+    "k_step": os.path.join(ROOT, "profiles", "step_traffic.txt"),
 }
 
 
 def main_kernel(ib_workgroups: int) -> str:
-    return "k_step_overlap" if ib_workgroups > 0 else "k_collide"
+    """k_step: the launches of a step taken together (k_step_macro, k_step_interp, k_step_band)."""
+    return "k_step" if ib_workgroups >= 0 else "k_collide"
 
 
 def kernel_source_hash(kernel: str) -> str:
@@ -450,7 +451,7 @@ def main():
     ap.add_argument("--batch-steps", type=int, default=200, help="batched form: steps per graph replay")
     ap.add_argument("--ib-steps", type=int, default=100, help="ib_schemes form: timed steps per scheme")
     ap.add_argument("--ib-workgroups", type=int, default=HEADLINE_IB_WORKGROUPS,
-                    help="headline step: immersed-boundary workgroups beside the collide (0: launches of their own)")
+                    help="headline step: -1 runs the immersed-boundary phases in launches of their own")
     args = ap.parse_args()
     world = int(os.environ.get("WORLD_SIZE", "1"))
     if args.gpus != 1 or world != 1:
@@ -458,7 +459,7 @@ def main():
               "build has no multi-GPU path", file=sys.stderr)
         sys.exit(2)
 
-    nib = max(0, args.ib_workgroups)
+    nib = args.ib_workgroups
     kernel = main_kernel(nib)
     main_run = run_gpu(args.storage, args.steps, args.warmup, tuple(args.block), ib_workgroups=nib)
     w = main_run["workload"]
@@ -467,11 +468,11 @@ def main():
     if "graph" in want:
         # the headline step loop as one captured graph, replayed
         forms["graph"] = run_graph(args.storage, args.steps, args.warmup, tuple(args.block), ib_workgroups=nib)
-    seq = main_run if nib == 0 else None
-    if nib > 0 and want & {"sequential", "ceiling"}:
+    seq = main_run if nib < 0 else None
+    if nib >= 0 and want & {"sequential", "ceiling"}:
         # the same step with the immersed-boundary phases in launches of their own before the collide: the
         # collide kernel alone against the roofline and the practical ceiling
-        seq = run_gpu(args.storage, args.steps, args.warmup, tuple(args.block), ib_workgroups=0)
+        seq = run_gpu(args.storage, args.steps, args.warmup, tuple(args.block), ib_workgroups=-1)
         t = measured_traffic(args.storage, "k_collide")
         forms["sequential"] = {"mlups": round(seq["mlups"], 1), "kernel": "k_collide",
                                "collide_avg_ms": round(seq["collide_avg_ms"], 5),
@@ -565,8 +566,8 @@ def main():
                      "avg_launch_ms": round(main_run["collide_avg_ms"], 5)},
         "step_hbm_frac": round(main_run["mlups"] * 1e6 * BYTES_PER_CELL[args.storage] / (HBM_PEAK_GBS * 1e9), 4),
         "ib_workgroups": nib,
-        # launches before the main one per step: every immersed-boundary phase (nib = 0); with the chain beside
-        # the collide, only the first step's skinning and tile binning, over all timed steps
+        # launches before the main ones per step: every immersed-boundary phase (nib = -1); beside the collide only
+        # the first step's skinning and tile binning, over all timed steps
         "pre_launch_ms_per_step": round(main_run["ib_avg_ms"], 5),
         "device_status": main_run["status"],
         "forms": forms,

@@ -157,7 +157,9 @@ typedef struct {
   int32_t block_x, block_y;  /* collide block: block_x (a multiple of 64) by block_y cells, or block_x
                                 consecutive cells of the x-fastest order when block_y = -1;
                                 0, 0 = default (256 consecutive cells with LBM_LAYOUT_ROWS,
-                                else 128 x 4 or 64 x 8) */
+                                else 512). The shape of the collide's own launch (no body,
+                                ib_workgroups = -1, batches, the adjoint); beside the
+                                immersed-boundary phases blocks are 256 consecutive cells */
   int32_t with_adjoint;      /* nonzero: workspace also holds the adjoint buffers */
   double tau;                /* BGK relaxation time, > 1/2 (nu = (tau - 1/2)/3) */
   double ib_alpha;           /* direct-forcing gain, > 0 (1 = full correction) */
@@ -167,10 +169,9 @@ typedef struct {
   double trt_lambda;         /* TRT: (tau - 1/2)(tau- - 1/2) > 0; unused by BGK */
   int32_t wall_mode;         /* LBM_WALL_*; 0 = no-slip */
   int32_t layout;            /* LBM_LAYOUT_*; 0 = automatic */
-  int32_t ib_workgroups;     /* direct forcing: > 0 runs the immersed-boundary phases in that many
-                                workgroups beside the collide, one launch per step (see lbm_ib_step),
-                                held to what the device runs at once (about two per compute unit);
-                                0 or -1 runs them before the collide in launches of their own */
+  int32_t ib_workgroups;     /* -1 .. 1024: -1 runs the immersed-boundary phases before the collide, each
+                                in a launch of its own; any other value runs them beside it (see
+                                lbm_ib_step), in as many workgroups as the library finds fit */
 } lbm_params;
 
 /* [host] Frame of one step (Eq. (3)). acc = linear acceleration of the frame
@@ -237,7 +238,9 @@ lbm_status lbm_init(lbm_ctx **out, const lbm_params *p, void *f_a, void *f_b, vo
  * it runs on until the process ends; the context itself is a per-device slot
  * of the library, so this call allocates no memory of any kind. Arguments as
  * lbm_init (f_a, f_b, rho0, u0, hip_stream) on the current device.
- * Errors: LBM_ERR_CAPACITY if lbm_workspace_bytes(p) exceeds
+ * Errors: LBM_ERR_CAPACITY if what the tiles, the markers and the options ask
+ * for (lbm_workspace_bytes(p) less the second body set, marker lists and wrench
+ * shares, for which the library holds room beside it) exceeds
  * LBM_STATIC_WORKSPACE_BYTES (lower max_markers or max_active_tiles);
  * LBM_ERR_ARG as lbm_init; LBM_ERR_DEVICE if the runtime cannot resolve the
  * array on this device.
@@ -286,14 +289,13 @@ lbm_status lbm_macros(lbm_ctx *c, const lbm_frame *frame, float *rho, float *u);
  *           sum F_k . U_k dV_k (1), 0. All float32.
  * Markers leaving the allowed region, and unstable states, are detected on the
  * device and reported by lbm_check.
- * Scheduling (lbm_params.ib_workgroups > 0): with direct forcing and a body
- * present, each step is one launch: ib_workgroups workgroups run the band
- * macros, interpolation and spreading, collide the cells whose source node
- * lies in an active tile (the only cells with an immersed force), then skin
- * and bin the next step's markers, while the others collide every other cell
- * without waiting, so the collide's streaming overlaps them; the first
- * step's skinning and binning run in launches of their own. By default every
- * phase runs in a launch of its own before the collide. The results are the
+ * Scheduling: with a body present, the immersed-boundary phases run beside the
+ * collide of the cells that carry no immersed force (all but those whose
+ * source node lies in an active tile, which collide after the spreading), and
+ * the next step's skinning and binning beside this step, in two or three
+ * launches per step with one forcing pass; the first step's skinning and
+ * binning run in launches of their own. lbm_params.ib_workgroups = -1 runs
+ * every phase in a launch of its own before the collide. The results are the
  * same bits either way. */
 lbm_status lbm_ib_step(lbm_ctx *c, const lbm_markers *m, const float *poses, const lbm_frame *frames,
                        int32_t nsteps, float *wrench);

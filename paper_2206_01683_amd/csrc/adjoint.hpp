@@ -176,14 +176,12 @@ __device__ inline void load_lam(const float *__restrict__ lam, const GridArgs &g
 }
 
 // ------------------------------------------------------------------ pass 1 --
-// gbar on the cells of active tile `slot` (state A in e.f[0]); clears the
-// tile's fixed-point IB adjoint accumulator.
+// gbar on the cells of active tile `slot` (state A in e.f[0]).
 __device__ inline void adj_gbar_item(const EnvView &e, const AdjArgs &A, int slot, int tid) {
   const GridArgs &g = e.g;
   const float *__restrict__ src = static_cast<const float *>(e.f[0]);
-  const int t = e.active[slot];
-  const int tx = t % g.tnx, ty = (t / g.tnx) % g.tny, tz = t / (g.tnx * g.tny);
-  const int x = tx * 8 + (tid & 7), y = ty * 8 + ((tid >> 3) & 7), z = tz * 8 + (tid >> 6);
+  const TileAt t = active_of(e.b[0], slot);
+  const int x = t.x * 8 + (tid & 7), y = t.y * 8 + ((tid >> 3) & 7), z = t.z * 8 + (tid >> 6);
   float gb[3] = {0.f, 0.f, 0.f};
   if (x < g.nx && y < g.ny && z < g.nz && (g.xper || (x > 0 && x < g.nx - 1))) {
     const int xm = g.xper ? wrap_idx(x - 1, g.nx) : x - 1;
@@ -194,7 +192,7 @@ __device__ inline void adj_gbar_item(const EnvView &e, const AdjArgs &A, int slo
     float rho, m[3];
     moments(f, rho, m[0], m[1], m[2]);
     float gg[3];
-    load_g(g, e.tile_slot, e.gfix, x, y, z, gg[0], gg[1], gg[2]);
+    load_g(g, e.b[0].tile_slot, e.gfix, x, y, z, gg[0], gg[1], gg[2]);
     const uint32_t row = (uint32_t)z * g.ny + y;
     float lam[Q];
     load_lam(A.lam_next, g, row, x, lam);
@@ -213,8 +211,6 @@ __device__ inline void adj_gbar_item(const EnvView &e, const AdjArgs &A, int slo
   gp[tid] = gb[0];
   gp[512 + tid] = gb[1];
   gp[1024 + tid] = gb[2];
-  unsigned long long *ap = A.adjfix + (size_t)slot * 2048;
-  for (int q = 0; q < 4; ++q) ap[q * 512 + tid] = 0ull;
 }
 
 // ------------------------------------------------------------------ pass 2 --
@@ -227,7 +223,7 @@ __device__ inline void adj_marker_item(const EnvView &e, const AdjArgs &A, int i
   const int n = e.n;
   if (k >= n) return;
   const GridArgs &g = e.g;
-  const float Xk[3] = {e.X[k], e.X[n + k], e.X[2 * n + k]};
+  const float Xk[3] = {e.b[0].X[k], e.b[0].X[n + k], e.b[0].X[2 * n + k]};
   const int s3[3] = {lane & 3, (lane >> 2) & 3, lane >> 4};
   const int dims[3] = {g.nx, g.ny, g.nz};
   int base[3], node[3];
@@ -241,7 +237,7 @@ __device__ inline void adj_marker_item(const EnvView &e, const AdjArgs &A, int i
     node[ax] = (ax > 0 || g.xper) ? wrap_idx(j, dims[ax]) : j;
   }
   const int t = (node[0] >> 3) + g.tnx * ((node[1] >> 3) + g.tny * (node[2] >> 3));
-  const int s = e.tile_slot[t];
+  const int s = e.b[0].tile_slot[t];
   float gb[3] = {0.f, 0.f, 0.f}, mac[4] = {1.f, 0.f, 0.f, 0.f};
   if (s >= 0) {
     const int lc = (node[0] & 7) | ((node[1] & 7) << 3) | ((node[2] & 7) << 6);
@@ -264,7 +260,7 @@ __device__ inline void adj_marker_item(const EnvView &e, const AdjArgs &A, int i
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     Fk[a] = e.F[a * n + k];
-    Uk[a] = e.U[a * n + k];
+    Uk[a] = e.b[0].U[a * n + k];
     Us[a] = e.mstate[(a + 1) * (size_t)n + k];
     Fb[a] = dvk * (G[a] - A.wF[a] + A.wP * Uk[a]);
     rkb += e.alpha2 * Fb[a] * (Uk[a] - Us[a]);
@@ -302,87 +298,9 @@ __device__ inline void adj_marker_item(const EnvView &e, const AdjArgs &A, int i
 }
 
 // ------------------------------------------------------------------ pass 3 --
-// Spreading of (rhobar_k, U*bar_k) onto active tile (slot, part), as
-// spread_item but with four components from record slots 15..18.
+// Spreading of (rhobar_k, U*bar_k), record slots 15..18.
 __device__ inline void adj_spread_item(const EnvView &e, const AdjArgs &A, int item, int tid) {
-  __shared__ unsigned long long s_acc[4][512];
-  const int lane = tid & 63, wv = tid >> 6;
-  const GridArgs &g = e.g;
-  const int n = e.n;
-  const int nchunks = (n + 63) >> 6;
-  const int slot = item / kSpreadSplit, part = item % kSpreadSplit;
-  const int t = e.active[slot];
-  const int tx = t % g.tnx, ty = (t / g.tnx) % g.tny, tz = t / (g.tnx * g.tny);
-  for (int q = tid; q < 4 * 512; q += WG) (&s_acc[0][0])[q] = 0ull;
-  __syncthreads();
-  const int stride = (WG / 64) * kSpreadSplit;
-  const int c_first = part * (WG / 64) + wv;
-  for (int it = 0; c_first + stride * 64 * it < nchunks; ++it) {
-    const int cl = c_first + stride * (lane + 64 * it);
-    bool pass = false;
-    if (cl < nchunks) {
-      const int4 box = e.chunk_box[cl];
-      pass = box_hits(box.x, tx) && box_hits(box.y, ty) && box_hits(box.z, tz);
-    }
-    unsigned long long cbal = __ballot(pass);
-    while (cbal) {
-      const int jc = __ffsll((long long)cbal) - 1;
-      cbal &= cbal - 1ull;
-      const int k = (c_first + stride * (jc + 64 * it)) * 64 + lane;
-      bool hit = false;
-      if (k < n) {
-        const short4 b = e.mbase[k];
-        hit = axis_touches(b.x, g.nx, g.xper, tx) && axis_touches(b.y, g.ny, true, ty) &&
-              axis_touches(b.z, g.nz, true, tz);
-      }
-      if (hit) {
-        float r[20];
-        const float4 *rp = reinterpret_cast<const float4 *>(e.rec + (size_t)k * REC);
-#pragma unroll
-        for (int q = 0; q < 5; ++q) {
-          const float4 v = rp[q];
-          r[4 * q] = v.x;
-          r[4 * q + 1] = v.y;
-          r[4 * q + 2] = v.z;
-          r[4 * q + 3] = v.w;
-        }
-        const int bx = __float_as_int(r[12]), by = __float_as_int(r[13]), bz = __float_as_int(r[14]);
-        int lx[4], ly[4], lz[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          int jx = bx + q, jy = wrap_idx(by + q, g.ny), jz = wrap_idx(bz + q, g.nz);
-          if (g.xper) jx = wrap_idx(jx, g.nx);
-          lx[q] = (jx >> 3) == tx ? (jx & 7) : -1;
-          ly[q] = (jy >> 3) == ty ? ((jy & 7) << 3) : -1;
-          lz[q] = (jz >> 3) == tz ? ((jz & 7) << 6) : -1;
-        }
-#pragma unroll
-        for (int qz = 0; qz < 4; ++qz) {
-          if (lz[qz] < 0) continue;
-#pragma unroll
-          for (int qy = 0; qy < 4; ++qy) {
-            if (ly[qy] < 0) continue;
-            const float wyz = r[4 + qy] * r[8 + qz];
-#pragma unroll
-            for (int qx = 0; qx < 4; ++qx) {
-              if (lx[qx] < 0) continue;
-              const float d = r[qx] * wyz;
-              const int lc = lx[qx] | ly[qy] | lz[qz];
-#pragma unroll
-              for (int cc = 0; cc < 4; ++cc) atomicAdd(&s_acc[cc][lc], to_fix(r[15 + cc] * d));
-            }
-          }
-        }
-      }
-    }
-  }
-  __syncthreads();
-  unsigned long long *ap = A.adjfix + (size_t)slot * 2048;
-  for (int q = tid; q < 4 * 512; q += WG) {
-    const unsigned long long v = (&s_acc[0][0])[q];
-    if (v != 0ull) atomicAdd(&ap[q], v);
-  }
-  __syncthreads();
+  spread_item<BT, false, 4, 15>(e, e.b[0], item, tid, A.adjfix, false);
 }
 
 // ------------------------------------------------------------------ pass 4 --
@@ -421,7 +339,7 @@ __device__ inline void adj_collide_cell(const EnvView &e, const AdjArgs &A, int 
     float rho, m[3];
     moments(f, rho, m[0], m[1], m[2]);
     float gg[3];
-    load_g(g, e.ib ? e.tile_slot : nullptr, e.gfix, x, y, z, gg[0], gg[1], gg[2]);
+    load_g(g, e.ib ? e.b[0].tile_slot : nullptr, e.gfix, x, y, z, gg[0], gg[1], gg[2]);
     float lam[Q];
     load_lam(A.lam_next, g, row, x, lam);
     float rb, mb[3], gb[3];
@@ -432,7 +350,7 @@ __device__ inline void adj_collide_cell(const EnvView &e, const AdjArgs &A, int 
     // through u* = m/rho + a0/2 and rho
     if (e.ib) {
       const int t = (x >> 3) + g.tnx * ((y >> 3) + g.tny * (z >> 3));
-      const int s = e.tile_slot[t];
+      const int s = e.b[0].tile_slot[t];
       if (s >= 0) {
         const int lc = (x & 7) | ((y & 7) << 3) | ((z & 7) << 6);
         const unsigned long long *ap = A.adjfix + (size_t)s * 2048;
@@ -508,7 +426,7 @@ __device__ inline void adj_face_item(const EnvView &e, const AdjArgs &A, int id)
   float rho, m[3];
   moments(f, rho, m[0], m[1], m[2]);
   float gg[3];
-  load_g(g, e.ib ? e.tile_slot : nullptr, e.gfix, x, y, z, gg[0], gg[1], gg[2]);
+  load_g(g, e.ib ? e.b[0].tile_slot : nullptr, e.gfix, x, y, z, gg[0], gg[1], gg[2]);
   float lam[Q];
   load_lam(A.lam_next, g, (uint32_t)yz, lo ? 0 : g.nx - 1, lam);
   float rb, mb[3], gb[3];
@@ -539,7 +457,7 @@ __global__ void __launch_bounds__(WG) k_adj_gbar(EnvView e, AdjArgs A, int face_
     return;
   }
   if (!e.ib) return;
-  const int na = n_active_of(e);
+  const int na = n_active_of(e, e.b[0]);
   const int nb = gridDim.x - face_blocks;
   for (int slot = blockIdx.x - face_blocks; slot < na; slot += nb) adj_gbar_item(e, A, slot, threadIdx.x);
 }
@@ -548,8 +466,8 @@ __global__ void __launch_bounds__(WG) k_adj_markers(EnvView e, AdjArgs A) {
   adj_marker_item(e, A, blockIdx.x, threadIdx.x);
 }
 
-__global__ void __launch_bounds__(WG) k_adj_spread(EnvView e, AdjArgs A) {
-  const int items = n_active_of(e) * kSpreadSplit;
+__global__ void __launch_bounds__(BT) k_adj_spread(EnvView e, AdjArgs A) {
+  const int items = kSpreadParts<BT> * n_active_of(e, e.b[0]);
   for (int item = blockIdx.x; item < items; item += gridDim.x) adj_spread_item(e, A, item, threadIdx.x);
 }
 

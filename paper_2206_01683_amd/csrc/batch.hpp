@@ -76,7 +76,7 @@ __device__ inline int find_env(const int *pre, int nenv, int item) {
 // more take the workgroup-wide scan.
 __device__ inline int dynamic_prefix(const BatchArgs &b, int mult, int *s_pre, int tid) {
   int v = 0;
-  if (tid < b.nenv) v = n_active_of(b.envs[tid]) * mult;
+  if (tid < b.nenv) v = n_active_of(b.envs[tid], b.envs[tid].b[0]) * mult;
   if (b.nenv <= 64) {
     if (tid < 64) {
       const int lane = tid;
@@ -127,17 +127,17 @@ template <bool TRT>
 __device__ inline void collide_any_t(const EnvView &e, const FrameF &fr, int cur, int lb, int tx, int ty) {
   if (!(e.g.yper && e.g.zper)) {
     if (e.g.xper)
-      e.rot ? collide_cell<StoreF32, true, true, true, TRT>(e, fr, cur, lb, tx, ty)
-            : collide_cell<StoreF32, true, false, true, TRT>(e, fr, cur, lb, tx, ty);
+      e.rot ? collide_cell<StoreF32, true, true, true, TRT>(e, e.b[0].tile_slot, fr, cur, lb, tx, ty)
+            : collide_cell<StoreF32, true, false, true, TRT>(e, e.b[0].tile_slot, fr, cur, lb, tx, ty);
     else
-      e.rot ? collide_cell<StoreF32, false, true, true, TRT>(e, fr, cur, lb, tx, ty)
-            : collide_cell<StoreF32, false, false, true, TRT>(e, fr, cur, lb, tx, ty);
+      e.rot ? collide_cell<StoreF32, false, true, true, TRT>(e, e.b[0].tile_slot, fr, cur, lb, tx, ty)
+            : collide_cell<StoreF32, false, false, true, TRT>(e, e.b[0].tile_slot, fr, cur, lb, tx, ty);
   } else if (e.g.xper) {
-    e.rot ? collide_cell<StoreF32, true, true, false, TRT>(e, fr, cur, lb, tx, ty)
-          : collide_cell<StoreF32, true, false, false, TRT>(e, fr, cur, lb, tx, ty);
+    e.rot ? collide_cell<StoreF32, true, true, false, TRT>(e, e.b[0].tile_slot, fr, cur, lb, tx, ty)
+          : collide_cell<StoreF32, true, false, false, TRT>(e, e.b[0].tile_slot, fr, cur, lb, tx, ty);
   } else {
-    e.rot ? collide_cell<StoreF32, false, true, false, TRT>(e, fr, cur, lb, tx, ty)
-          : collide_cell<StoreF32, false, false, false, TRT>(e, fr, cur, lb, tx, ty);
+    e.rot ? collide_cell<StoreF32, false, true, false, TRT>(e, e.b[0].tile_slot, fr, cur, lb, tx, ty)
+          : collide_cell<StoreF32, false, false, false, TRT>(e, e.b[0].tile_slot, fr, cur, lb, tx, ty);
   }
 }
 
@@ -172,27 +172,27 @@ __device__ inline void collide_item(const EnvView &e, const FrameF &fr, int cur,
     collide_any(e, fr, cur, lb, tx, ty);
   else
     collide_cell<typename StoreOf<(K >> 4)>::type, (K & 1) != 0, (K & 2) != 0, (K & 4) != 0, (K & 8) != 0>(
-        e, fr, cur, lb, tx, ty);
+        e, e.b[0].tile_slot, fr, cur, lb, tx, ty);
 }
 
 // ------------------------------------------------------------ phase bodies --
 __device__ inline void phase_skin(const BatchArgs &b, int s, int item, int tid) {
   const int ei = find_env(b.pre + PRE_SKIN * (b.nenv + 1), b.nenv, item);
   const EnvView &e = b.envs[ei];
-  skin_item(e, e.poses + (size_t)s * e.nbones * 24, item - b.pre[PRE_SKIN * (b.nenv + 1) + ei], tid);
+  skin_item(e, e.b[0], e.poses + (size_t)s * e.nbones * 24, item - b.pre[PRE_SKIN * (b.nenv + 1) + ei], tid);
 }
 
 __device__ inline void phase_active(const BatchArgs &b, int item, int tid) {
   const int ei = find_env(b.pre + PRE_ACTIVE * (b.nenv + 1), b.nenv, item);
-  active_item(b.envs[ei], item - b.pre[PRE_ACTIVE * (b.nenv + 1) + ei], tid);
+  active_item(b.envs[ei], b.envs[ei].b[0], item - b.pre[PRE_ACTIVE * (b.nenv + 1) + ei], tid);
 }
 
 template <class S, bool UNI>
 __device__ inline void macro_rot(const EnvView &e, const FrameF &fr, int cur, int slot, int tid) {
   if (!UNI && e.rot)
-    macro_item<S, true>(e, fr, cur, slot, tid);
+    macro_item<WG, S, true>(e, e.b[0], fr, cur, slot, tid);
   else
-    macro_item<S, false>(e, fr, cur, slot, tid);
+    macro_item<WG, S, false>(e, e.b[0], fr, cur, slot, tid);
 }
 
 // ANYS: environments may store 2-byte populations (per-phase driver); the
@@ -203,6 +203,7 @@ __device__ inline void phase_macro(const BatchArgs &b, int s, int item, const in
   const EnvView &e = b.envs[ei];
   const FrameF fr = env_frame(e, s);
   const int cur = env_cur(e, s), slot = item - s_pre[ei];
+  list_item<WG>(e, e.b[0], slot, tid);
   if (!UNI && ANYS && e.storage == StoreF16::kind)
     macro_rot<StoreF16, UNI>(e, fr, cur, slot, tid);
   else if (!UNI && ANYS && e.storage == StoreBF16::kind)
@@ -220,27 +221,27 @@ __device__ inline void phase_interp(const BatchArgs &b, int s, int pass, int ite
   float *part = (e.wrench != nullptr && pass == b.mdf - 1) ? e.partials : nullptr;
   if (!UNI && e.rot) {
     if (pass > 0)
-      interp_item<true, true>(e, fr, local, tid, part);
+      interp_item<WG, true, true>(e, e.b[0], fr, local, tid, part);
     else
-      interp_item<true, false>(e, fr, local, tid, part);
+      interp_item<WG, true, false>(e, e.b[0], fr, local, tid, part);
   } else {
     if (pass > 0)
-      interp_item<false, true>(e, fr, local, tid, part);
+      interp_item<WG, false, true>(e, e.b[0], fr, local, tid, part);
     else
-      interp_item<false, false>(e, fr, local, tid, part);
+      interp_item<WG, false, false>(e, e.b[0], fr, local, tid, part);
   }
 }
 
-// final: the step's last spreading pass; its first item per environment also
+// add: on top of the earlier passes' force. final: the step's last spreading pass; its first item per environment also
 // sums the wrench partials.
-__device__ inline void phase_spread(const BatchArgs &b, int s, bool final_pass, int item, const int *s_pre,
+__device__ inline void phase_spread(const BatchArgs &b, int s, bool final_pass, bool add, int item, const int *s_pre,
                                     int tid) {
   const int ei = find_env(s_pre, b.nenv, item);
   const EnvView &e = b.envs[ei];
   const int local = item - s_pre[ei];
   if (final_pass && local == 0 && e.wrench != nullptr)
-    wrench_sum(e.partials, interp_items(e.n), e.wrench + (size_t)8 * s, tid);
-  spread_item<kBatchSpreadSplit>(e, local, tid);
+    wrench_sum<WG>(e.partials, e.n, e.wrench + (size_t)8 * s, tid);
+  spread_item<WG, false>(e, e.b[0], local, tid, e.gfix, add);
 }
 
 // Collide item -> (environment, logical block); 512 threads as e.bx x e.by.
@@ -294,19 +295,19 @@ __global__ void __launch_bounds__(kCgWG) kb_cg_init(BatchArgs b, int s) {
   const EnvView &e = b.envs[ei];
   const FrameF fr = env_frame(e, s);
   if (e.rot)
-    cg_init_item<true>(e, fr, blockIdx.x - pre[ei]);
+    cg_init_item<true>(e, e.b[0], fr, blockIdx.x - pre[ei]);
   else
-    cg_init_item<false>(e, fr, blockIdx.x - pre[ei]);
+    cg_init_item<false>(e, e.b[0], fr, blockIdx.x - pre[ei]);
 }
 
 // Spreading of CG step j's search direction into each environment's gcg.
 __global__ void __launch_bounds__(WG) kb_spread_cg(BatchArgs b, int j) {
   __shared__ int s_pre[kMaxEnvs + 1];
-  const int tot = dynamic_prefix(b, kBatchSpreadSplit, s_pre, threadIdx.x);
+  const int tot = dynamic_prefix(b, kSpreadParts<WG>, s_pre, threadIdx.x);
   for (int item = blockIdx.x; item < tot; item += gridDim.x) {
     const int ei = find_env(s_pre, b.nenv, item);
     const EnvView &e = b.envs[ei];
-    spread_item<true, kBatchSpreadSplit>(e, item - s_pre[ei], threadIdx.x, e.gcg, cg_scal(e, 1, j), j == 0);
+    spread_item<WG, true>(e, e.b[0], item - s_pre[ei], threadIdx.x, e.gcg, false, cg_scal(e, 1, j), j == 0);
   }
 }
 
@@ -315,7 +316,7 @@ __global__ void __launch_bounds__(WG) kb_cg_apply(BatchArgs b, int j) {
   const int *pre = b.pre + PRE_INTERP * (b.nenv + 1);
   const int item = xcd_item(blockIdx.x, gridDim.x);
   const int ei = find_env(pre, b.nenv, item);
-  cg_apply_item(b.envs[ei], item - pre[ei], threadIdx.x, j);
+  cg_apply_item(b.envs[ei], b.envs[ei].b[0], item - pre[ei], threadIdx.x, j);
 }
 
 // Grid: the total of PRE_CG.
@@ -323,18 +324,7 @@ __global__ void __launch_bounds__(kCgWG) kb_cg_update(BatchArgs b, int s, int j,
   const int *pre = b.pre + PRE_CG * (b.nenv + 1);
   const int ei = find_env(pre, b.nenv, blockIdx.x);
   const EnvView &e = b.envs[ei];
-  cg_update_item(e, env_frame(e, s), blockIdx.x - pre[ei], j, last != 0);
-}
-
-// Clears gcg of every active tile before the next CG step's spreading.
-__global__ void __launch_bounds__(WG) kb_cg_clear(BatchArgs b) {
-  __shared__ int s_pre[kMaxEnvs + 1];
-  const int tot = dynamic_prefix(b, 1, s_pre, threadIdx.x);
-  for (int item = blockIdx.x; item < tot; item += gridDim.x) {
-    const int ei = find_env(s_pre, b.nenv, item);
-    unsigned long long *gq = b.envs[ei].gcg + (size_t)(item - s_pre[ei]) * 1536;
-    for (int q = threadIdx.x; q < 1536; q += WG) gq[q] = 0ull;
-  }
+  cg_update_item(e, e.b[0], env_frame(e, s), blockIdx.x - pre[ei], j, last != 0);
 }
 
 // ------------------------------------------------------ per-phase kernels --
@@ -356,11 +346,11 @@ __global__ void __launch_bounds__(WG) kb_interp(BatchArgs b, int s, int pass) {
   phase_interp<UNI>(b, s, pass, xcd_item(blockIdx.x, gridDim.x), threadIdx.x);
 }
 
-__global__ void __launch_bounds__(WG) kb_spread(BatchArgs b, int s, int final_pass) {
+__global__ void __launch_bounds__(WG) kb_spread(BatchArgs b, int s, int final_pass, int add) {
   __shared__ int s_pre[kMaxEnvs + 1];
-  const int tot = dynamic_prefix(b, kBatchSpreadSplit, s_pre, threadIdx.x);
+  const int tot = dynamic_prefix(b, kSpreadParts<WG>, s_pre, threadIdx.x);
   for (int item = blockIdx.x; item < tot; item += gridDim.x)
-    phase_spread(b, s, final_pass != 0, item, s_pre, threadIdx.x);
+    phase_spread(b, s, final_pass != 0, add != 0, item, s_pre, threadIdx.x);
 }
 
 // Collide items item0 .. item0 + gridDim.x - 1, all of environments of kind
@@ -478,12 +468,12 @@ __global__ void __launch_bounds__(WG, 6) kb_persistent(BatchArgs b, int nsteps) 
     int tot;
     {
       const int tid = phase_tid();
-      tot = dynamic_prefix(b, kBatchSpreadSplit, s_pre, tid);
+      tot = dynamic_prefix(b, kSpreadParts<WG>, s_pre, tid);
     }
     for (int pass = 0; pass < b.mdf; ++pass) {
       if (pass > 0) {
         const int tid = phase_tid(), blk = phase_blk(), grid = phase_grid();
-        for (int item = blk; item < tot; item += grid) phase_spread(b, s, false, item, s_pre, tid);
+        for (int item = blk; item < tot; item += grid) phase_spread(b, s, false, pass > 1, item, s_pre, tid);
         if (!grid_sync(b)) return;
       }
       {
@@ -495,7 +485,7 @@ __global__ void __launch_bounds__(WG, 6) kb_persistent(BatchArgs b, int nsteps) 
     }
     {
       const int tid = phase_tid(), blk = phase_blk(), grid = phase_grid();
-      for (int item = blk; item < tot; item += grid) phase_spread(b, s, true, item, s_pre, tid);
+      for (int item = blk; item < tot; item += grid) phase_spread(b, s, true, b.mdf > 1, item, s_pre, tid);
     }
     if (!grid_sync(b)) return;
     {

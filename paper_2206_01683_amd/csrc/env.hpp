@@ -29,6 +29,19 @@ struct TrtRates {
   float wp, wm, pp, pm, a, b;
 };
 
+// What one step's skinning and binning produce. A context holds two sets and
+// steps alternate between them, so that a launch of one step can skin and bin
+// the next step's markers while it still reads its own.
+struct BodySet {
+  float *X, *U;     // marker positions and velocities, [3][n]
+  float *Nrm;       // [3][n] skinned unit normals (slip walls)
+  short4 *mbase;    // stencil base node of each marker
+  int4 *chunk_box;  // tile range of each 64 consecutive markers
+  int *tile_slot;   // slot of each tile, -1 when inactive
+  int4 *active;     // per slot: tx | ty << 16, tz, first entry and length of its marker list
+  int *counters;    // [0] active tiles, [1] arrivals of the implicit correction, [2] list entries
+};
+
 struct EnvView {
   GridArgs g;
   float inv_tau, omt, pref;     // 1/tau, 1 - 1/tau, 1 - 1/(2 tau)
@@ -44,16 +57,15 @@ struct EnvView {
   const float *xrest, *weight, *dv;
   int slip;                     // slip wall: force along the skinned normals Nrm only
   const float *nrest;           // [3][n] rest normals (slip)
-  float *Nrm;                   // [3][n] skinned unit normals of this step (slip)
   const int *bone;
-  float *X, *U, *F;
-  int *tile_flag, *tile_slot, *active, *counters, *guard;
-  short4 *mbase;
-  int4 *chunk_box;
+  BodySet b[2];                 // b[0]: this step's body in the single-lattice kernels, b[1]: the next step's
+  float *F;
+  int *tile_flag;               // tiles some stencil touches: set by the skinning, cleared by the binning
+  int *list;                    // marker lists of the active tiles (see list_item)
+  int *guard;
   float *partials;
   float4 *macro;
   unsigned long long *gfix;
-  unsigned *sched;              // scheduling words of the overlapped step (single lattice), or null
   float *rec, *mstate;
   // implicit velocity correction (null with direct forcing)
   unsigned long long *gcg;      // fixed-point spread of the search direction, as gfix

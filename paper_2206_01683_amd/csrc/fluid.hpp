@@ -174,15 +174,16 @@ __device__ inline bool collide_load(const EnvView &e, int cur, int lb, int tx, i
 // and the 27 stores of f*(n). TRT: the two-relaxation-time collision instead
 // of BGK (even and odd parts of f relax at omega+ and omega-, Guo's source
 // split the same way).
+// (gx, gy, gz): the immersed force density at the source node.
 template <class S, bool XPER, bool ROT, bool YZ = false, bool TRT = false>
-__device__ inline void collide_finish(const EnvView &e, const FrameF &fr, int cur, const CellAt &c, float f[Q]) {
+__device__ inline void collide_finish(const EnvView &e, const FrameF &fr, int cur, const CellAt &c, float f[Q],
+                                      float gx, float gy, float gz) {
   // multiply-adds fused within a source expression only, so that this
   // arithmetic rounds the same way in every kernel it is inlined into (the
   // single-lattice, batched and persistent collides give the same bits)
 #pragma clang fp contract(on)
   using T = typename S::T;
   gmem<T> *__restrict__ dst = (gmem<T> *)e.f[cur ^ 1];
-  const int *__restrict__ tile_slot = e.ib ? e.tile_slot : nullptr;
   const GridArgs &g = e.g;
   const int x = c.x, y = c.y, z = c.z, xs = c.xs;
   const int ys = YZ ? c.ys : y, zs = YZ ? c.zs : z;
@@ -194,8 +195,6 @@ __device__ inline void collide_finish(const EnvView &e, const FrameF &fr, int cu
   const float rho = 1.0f + drho;
   const float irho = 1.0f / rho;
 
-  float gx, gy, gz;
-  load_g(g, tile_slot, e.gfix, xs, ys, zs, gx, gy, gz);
   float ax, ay, az;
   frame_a0<ROT>(fr, (float)xs, (float)ys, (float)zs, ax, ay, az);
   float ux, uy, uz;
@@ -306,12 +305,17 @@ __device__ inline void collide_finish(const EnvView &e, const FrameF &fr, int cu
 }
 
 // One cell of logical block lb (tile shape e.bx x e.by, see cell_of), thread
-// (tx, ty); `cur` is the buffer holding f*(n-1), the other one receives f*(n).
+// (tx, ty); `cur` is the buffer holding f*(n-1), the other one receives f*(n);
+// tile_slot: this step's tile map.
 template <class S, bool XPER, bool ROT, bool YZ = false, bool TRT = false>
-__device__ inline void collide_cell(const EnvView &e, const FrameF &fr, int cur, int lb, int tx, int ty) {
+__device__ inline void collide_cell(const EnvView &e, const int *tile_slot, const FrameF &fr, int cur, int lb, int tx,
+                                    int ty) {
   CellAt c;
   float f[Q];
-  if (collide_load<S, XPER, YZ>(e, cur, lb, tx, ty, c, f)) collide_finish<S, XPER, ROT, YZ, TRT>(e, fr, cur, c, f);
+  if (!collide_load<S, XPER, YZ>(e, cur, lb, tx, ty, c, f)) return;
+  float gx, gy, gz;
+  load_g(e.g, e.ib ? tile_slot : nullptr, e.gfix, c.xs, c.ys, c.zs, gx, gy, gz);
+  collide_finish<S, XPER, ROT, YZ, TRT>(e, fr, cur, c, f, gx, gy, gz);
 }
 
 // Single-lattice launch: blockDim = (e.bx, e.by), logical block = hardware
@@ -323,7 +327,7 @@ template <class S, bool XPER, bool ROT, bool YZ = false, bool TRT = false>
 __global__ void __launch_bounds__(512) k_collide(EnvView e, FrameF fr, int cur) {
   const int lb = blockIdx.x;
   if (lb >= e.nblocks) return;
-  collide_cell<S, XPER, ROT, YZ, TRT>(e, fr, cur, lb, threadIdx.x, threadIdx.y);
+  collide_cell<S, XPER, ROT, YZ, TRT>(e, e.b[0].tile_slot, fr, cur, lb, threadIdx.x, threadIdx.y);
 }
 
 // f_i(x) of the caller's canonical pre-collision field -> stored buffer, i.e.
@@ -364,6 +368,15 @@ __global__ void k_init_equilibrium(const float *__restrict__ rho0, const float *
     float v = w_of(i) * r * (1.0f + 3.0f * cu + 4.5f * cu * cu - 1.5f * (ux * ux + uy * uy + uz * uz));
     S::store_plain(dst + pop_idx(g, i, (uint32_t)z * g.ny + y, x), v, i);
   }
+}
+
+// Zeroes the elements of a population buffer that hold no population, so that
+// a buffer can be read as a whole. One workgroup per plane of the buffer.
+template <class S>
+__global__ void k_clear_padding(typename S::T *__restrict__ buf, GridArgs g) {
+  const size_t n = (size_t)g.nx * g.ny * g.nz, pad = g.plane - n, i = blockIdx.x;
+  const size_t at = g.ps == g.plane ? i * g.plane + n : Q * n + i * pad;  // planes : rows
+  for (size_t q = threadIdx.x; q < pad; q += blockDim.x) buf[at + q] = typename S::T(0);
 }
 
 // Stored buffer -> canonical pre-collision populations (pull with wrap/clamp).

@@ -4,23 +4,24 @@
 // The immersed force lives only in "active" 8x8x8 tiles: tiles that some
 // marker's 4x4x4 Peskin stencil touches. Each step rebuilds the active set.
 // Every phase is a device function of (environment, work item) run by one
-// 512-thread workgroup, so the same code serves the single-lattice kernels,
-// the batched per-phase kernels and the persistent batched kernel:
+// workgroup, so the same code serves the single-lattice kernels, the batched
+// per-phase kernels and the persistent batched kernel:
 //   skin_item     512 markers: linear blend skinning, wrap/range guard, flag
 //                 the tiles each stencil touches (plain stores), per-wave
 //                 chunk boxes (tile range of 64 consecutive markers)
 //   active_item   512 tiles: compact the flags into slots and an active list
+//   list_item     one active tile: the list of the markers that touch it
 //   macro_item    one active tile: density and unforced velocity of its 512
-//                 cells; clears the tile's fixed-point force
-//   interp_item   32 markers, 16 lanes each, one lane per x-row of 4
-//                 stencil nodes: row sums, then 16-lane sums -> U*_k, rho_k,
-//                 direct forcing F_k, marker record, wrench partials
-//   spread_item   (active tile, part): the markers whose stencils touch the
-//                 tile add their stencil nodes into an LDS tile in 64-bit fixed
-//                 point (order-independent, so deterministic), merged into the
-//                 tile's fixed-point force with one atomic per nonzero cell
+//                 cells
+//   interp_item,  U*_k, rho_k, direct forcing F_k, marker record, wrench
+//   interp_wave   shares; from the band macros, or straight from the populations
+//   spread_planes one z-plane of an active tile per 256 threads: its markers add
+//                 their stencil nodes into LDS in 64-bit fixed point
+//                 (order-independent, so deterministic)
 //   wrench_sum    adds the wrench partials in a fixed order
 #pragma once
+
+#include <type_traits>
 
 #include "fluid.hpp"
 
@@ -28,16 +29,9 @@ namespace lbmib {
 
 constexpr int WG = 512;              // threads per workgroup in every IB phase
 constexpr int REC = 20;              // floats per marker record: w[12], base[3], pad, fdv[3], pad
-constexpr int kSpreadSplit = 4;      // spreading work items per active tile (single lattice)
-constexpr int kBatchSpreadSplit = 2; // the same in the batched forms, whose many tiles need less splitting
 constexpr int kWavePer = WG / 64;    // markers per item of the one-wave-per-marker kernels (adjoint)
-constexpr int kInterpMk = WG / 16;   // markers per interpolation (and CG apply) item, 16 lanes each
-
-// Scheduling words of the overlapped step (step.hpp), each on its own
-// 128-byte line, in the workspace (EnvView::sched): the chain's barrier
-// arrival count and generation. k_active clears the arrival count.
-constexpr int kSchedLine = 32;
-enum : int { SCHED_ARRIVE = 0, SCHED_GEN = kSchedLine, SCHED_WORDS = 2 * kSchedLine };
+constexpr int kInterpMk = WG / 16;   // markers per CG apply item, 16 lanes each
+constexpr int BT = 256;              // threads per workgroup of the single-lattice marker phases
 
 __device__ inline int stencil_base(float X) { return (int)floorf(X) - 1; }
 
@@ -56,15 +50,19 @@ __device__ inline void axis_node_tiles(int base, int n, bool per, int t[4], bool
   }
 }
 
-__device__ inline bool axis_touches(int base, int n, bool per, int tile) {
-  bool hit = false;
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    int j = base + s;
-    if (per) j = wrap_idx(j, n);
-    hit |= (j >> 3) == tile;
-  }
-  return hit;
+// Most tiles a stencil touches along an axis of n nodes: two, or three where
+// it wraps across a last tile of one or two nodes.
+__host__ __device__ inline int axis_tiles_most(int n) {
+  const int tiles = (n + 7) >> 3, most = (n & 7) == 1 || (n & 7) == 2 ? 3 : 2;
+  return tiles < most ? tiles : most;
+}
+
+// (base + 3 - lo) modulo n for base in -1 .. n-2. The stencil base..base+3
+// (taken modulo n) has a node in the tile at lo exactly where this is below the
+// tile's width plus three.
+__device__ inline int axis_from(int base, int n, int lo) {
+  const int d = base + 3 - lo;
+  return d < 0 ? d + n : (d >= n ? d - n : d);
 }
 
 // Value of lane (this lane ^ o) of the wave (ds_bpermute). The lane id
@@ -88,21 +86,23 @@ __device__ inline float wave_sum(float v) {
 __device__ inline bool box_hits(int packed, int t) { return t >= (packed & 0xFFFF) && t <= (packed >> 16); }
 
 // --------------------------------------------------------------- skinning --
-// Markers 512*item .. 512*item+511 with bone poses `pose` of this step.
-// Linear blend skinning X = sum_b w_b (R_b xrest + t_b), U = sum_b w_b
+// Markers NT*item .. NT*item + NT - 1 with bone poses `pose` into the body set
+// bs. Linear blend skinning X = sum_b w_b (R_b xrest + t_b), U = sum_b w_b
 // (dR_b xrest + dt_b). Periodic axes: X wrapped into [0, n). Open x: markers
 // must satisfy 2 <= X < nx - 3 so the stencil stays on nodes 1 .. nx-2; others
 // raise the range guard and are clamped so that every access stays in bounds.
-// Item 0 also clears the active-tile counter of this step. (Always inlined:
-// called as a function, its call would hold the persistent kernel's registers
-// across it and push that kernel past its budget.)
-__device__ __attribute__((always_inline)) inline void skin_item(const EnvView &e, const float *__restrict__ pose,
-                                                                int item, int tid) {
-  const int k = item * WG + tid;
+// Item 0 also clears the set's counters. (Always inlined: called as a
+// function, its call would hold the persistent kernel's registers across it
+// and push that kernel past its budget.)
+template <int NT = WG>
+__device__ __attribute__((always_inline)) inline void skin_item(const EnvView &e, const BodySet &bs,
+                                                                const float *__restrict__ pose, int item, int tid) {
+  const int k = item * NT + tid;
   const int n = e.n;
   if (k == 0) {
-    e.counters[0] = 0;  // active tiles of this step
-    e.counters[1] = 0;  // arrival count of the implicit correction's reductions
+    bs.counters[0] = 0;  // active tiles of this step
+    bs.counters[1] = 0;  // arrival count of the implicit correction's reductions
+    bs.counters[2] = 0;  // entries of the marker lists
   }
   const int tns[3] = {e.g.tnx, e.g.tny, (e.g.nz + 7) >> 3};
   const int dims[3] = {e.g.nx, e.g.ny, e.g.nz};
@@ -111,7 +111,7 @@ __device__ __attribute__((always_inline)) inline void skin_item(const EnvView &e
   const gmem<float> *xrest = (const gmem<float> *)e.xrest, *nrest = (const gmem<float> *)e.nrest;
   const gmem<float> *weight = (const gmem<float> *)e.weight, *gpose = (const gmem<float> *)pose;
   const gmem<int> *bone = (const gmem<int> *)e.bone;
-  gmem<float> *X = (gmem<float> *)e.X, *U = (gmem<float> *)e.U;
+  gmem<float> *X = (gmem<float> *)bs.X, *U = (gmem<float> *)bs.U;
   gmem<int> *tile_flag = (gmem<int> *)e.tile_flag;
   if (k < n) {
     const float r0 = xrest[k], r1 = xrest[n + k], r2 = xrest[2 * n + k];
@@ -145,7 +145,7 @@ __device__ __attribute__((always_inline)) inline void skin_item(const EnvView &e
     if (e.slip) {  // the rest normal turned by the blended rotations, unit length
       const float il = rsqrtf(nv[0] * nv[0] + nv[1] * nv[1] + nv[2] * nv[2]);
 #pragma unroll
-      for (int r = 0; r < 3; ++r) ((gmem<float> *)e.Nrm)[r * n + k] = nv[r] * il;
+      for (int r = 0; r < 3; ++r) ((gmem<float> *)bs.Nrm)[r * n + k] = nv[r] * il;
     }
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
@@ -162,17 +162,17 @@ __device__ __attribute__((always_inline)) inline void skin_item(const EnvView &e
       X[ax * n + k] = p[ax];
       U[ax * n + k] = v[ax];
     }
-    const int bs[3] = {stencil_base(p[0]), stencil_base(p[1]), stencil_base(p[2])};
-    gmem<short> *mb = (gmem<short> *)e.mbase + 4 * (size_t)k;
-    mb[0] = (short)bs[0];
-    mb[1] = (short)bs[1];
-    mb[2] = (short)bs[2];
+    const int bs3[3] = {stencil_base(p[0]), stencil_base(p[1]), stencil_base(p[2])};
+    gmem<short> *mb = (gmem<short> *)bs.mbase + 4 * (size_t)k;
+    mb[0] = (short)bs3[0];
+    mb[1] = (short)bs3[1];
+    mb[2] = (short)bs3[2];
     mb[3] = 0;
     int tx[4], ty[4], tz[4];
     bool fx[4], fy[4], fz[4];
-    axis_node_tiles(bs[0], e.g.nx, e.g.xper, tx, fx);
-    axis_node_tiles(bs[1], e.g.ny, e.g.yper, ty, fy);
-    axis_node_tiles(bs[2], e.g.nz, e.g.zper, tz, fz);
+    axis_node_tiles(bs3[0], e.g.nx, e.g.xper, tx, fx);
+    axis_node_tiles(bs3[1], e.g.ny, e.g.yper, ty, fy);
+    axis_node_tiles(bs3[2], e.g.nz, e.g.zper, tz, fz);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -182,12 +182,12 @@ __device__ __attribute__((always_inline)) inline void skin_item(const EnvView &e
           if (fz[i] && fy[j] && fx[l]) tile_flag[tx[l] + e.g.tnx * (ty[j] + e.g.tny * tz[i])] = 1;
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-      if (bs[ax] < 0 || bs[ax] + 3 >= dims[ax]) {  // wrapping stencil: whole axis
+      if (bs3[ax] < 0 || bs3[ax] + 3 >= dims[ax]) {  // wrapping stencil: whole axis
         lo[ax] = 0;
         hi[ax] = tns[ax] - 1;
       } else {
-        lo[ax] = bs[ax] >> 3;
-        hi[ax] = (bs[ax] + 3) >> 3;
+        lo[ax] = bs3[ax] >> 3;
+        hi[ax] = (bs3[ax] + 3) >> 3;
       }
     }
   }
@@ -200,7 +200,7 @@ __device__ __attribute__((always_inline)) inline void skin_item(const EnvView &e
     }
   }
   if ((tid & 63) == 0 && k < n) {
-    gmem<int> *cb = (gmem<int> *)e.chunk_box + 4 * (size_t)(k >> 6);
+    gmem<int> *cb = (gmem<int> *)bs.chunk_box + 4 * (size_t)(k >> 6);
     cb[0] = lo[0] | (hi[0] << 16);
     cb[1] = lo[1] | (hi[1] << 16);
     cb[2] = lo[2] | (hi[2] << 16);
@@ -208,24 +208,21 @@ __device__ __attribute__((always_inline)) inline void skin_item(const EnvView &e
   }
 }
 
-__device__ __host__ inline int skin_items(int n) { return (n + WG - 1) / WG; }
+template <int NT = WG>
+__device__ __host__ inline int skin_items(int n) {
+  return (n + NT - 1) / NT;
+}
 
 // ---------------------------------------------------------- active tiles --
-// Tiles 512*item .. 512*item+511: slots in workgroup order from one atomic per
-// workgroup. Slot numbering only decides storage locations, never results.
-// Clears the flags for the next step. slots: the tile map to write (null:
-// e.tile_slot). reset_sched: item 0 also clears the overlapped step's barrier
-// count (not when the overlapped step itself bins the next step's tiles).
-__device__ inline void active_item(const EnvView &e, int item, int tid, bool reset_sched = true,
-                                   int *slots = nullptr) {
-  __shared__ int s_w[WG / 64];
+// Tiles NT*item .. NT*item + NT - 1 of the set bs: slots in workgroup order
+// from one atomic per workgroup. Slot numbering only decides storage locations,
+// never results. Clears the flags for the next step.
+template <int NT = WG>
+__device__ inline void active_item(const EnvView &e, const BodySet &bs, int item, int tid) {
+  __shared__ int s_w[NT / 64];
   __shared__ int s_base;
   const int lane = tid & 63, wv = tid >> 6;
-  const int t = item * WG + tid;
-  if (item == 0 && tid == 0 && e.sched != nullptr && reset_sched) {
-    e.sched[SCHED_ARRIVE] = 0u;
-  }
-  int *tile_slot = slots != nullptr ? slots : e.tile_slot;
+  const int t = item * NT + tid;
   int f = 0;
   if (t < e.ntiles) {
     f = e.tile_flag[t] != 0;
@@ -236,8 +233,8 @@ __device__ inline void active_item(const EnvView &e, int item, int tid, bool res
   __syncthreads();
   if (tid == 0) {
     int tot = 0;
-    for (int q = 0; q < WG / 64; ++q) tot += s_w[q];
-    s_base = tot ? atomicAdd(&e.counters[0], tot) : 0;
+    for (int q = 0; q < NT / 64; ++q) tot += s_w[q];
+    s_base = tot ? atomicAdd(&bs.counters[0], tot) : 0;
   }
   __syncthreads();
   int pre = s_base;
@@ -245,18 +242,35 @@ __device__ inline void active_item(const EnvView &e, int item, int tid, bool res
   pre += __popcll(bal & ((1ull << lane) - 1ull));
   if (t < e.ntiles) {
     if (f && pre < e.cap) {
-      tile_slot[t] = pre;
-      e.active[pre] = t;
+      bs.tile_slot[t] = pre;
+      const int tx = t % e.g.tnx, rest = t / e.g.tnx;
+      bs.active[pre] = make_int4(tx | ((rest % e.g.tny) << 16), rest / e.g.tny, 0, 0);
     } else {
-      tile_slot[t] = -1;
+      bs.tile_slot[t] = -1;
       if (f) atomicOr(e.guard, (int)GUARD_CAPACITY);
     }
   }
   __syncthreads();  // s_w / s_base are reused by the next item
 }
 
-__device__ inline int active_items(const EnvView &e) { return (e.ntiles + WG - 1) / WG; }
-__device__ inline int n_active_of(const EnvView &e) { return min(e.counters[0], e.cap); }
+template <int NT = WG>
+__device__ __host__ inline int active_items(const EnvView &e) {
+  return (e.ntiles + NT - 1) / NT;
+}
+__device__ inline int n_active_of(const EnvView &e, const BodySet &bs) {
+  return min(((const gmem<int> *)bs.counters)[0], e.cap);
+}
+// Coordinates of a slot's tile (stored as such: a band workgroup needs them
+// first, and two integer divisions are a third of its index arithmetic) and
+// its marker list.
+struct TileAt {
+  int x, y, z, off, cnt;
+};
+__device__ inline TileAt active_of(const BodySet &bs, int slot) {
+  const gmem<int> *p = (const gmem<int> *)bs.active + 4 * (size_t)slot;
+  const int xy = p[0];
+  return {xy & 0xFFFF, xy >> 16, p[1], p[2], p[3]};
+}
 
 // XCD-contiguous walk over work items 0 .. tot-1. The dispatcher hands
 // workgroup b to XCD b % kXcds, and each XCD has its own L2; an active tile's
@@ -289,18 +303,130 @@ __device__ inline int xcd_item(int blk, int grid) {
   return x * q + min(x, m) + blk / kXcds;
 }
 
+// ----------------------------------------------------------- marker lists --
+// Appends v to list[*count ...] for the lanes of this wave with `take`, below
+// most entries; *count counts them all.
+__device__ inline void wave_push(bool take, int v, int *list, int *count, int most, int lane) {
+  const unsigned long long bal = __ballot(take);
+  if (bal == 0ull) return;
+  int at = 0;
+  if (lane == 0) at = atomicAdd(count, (int)__popcll(bal));
+  at = __builtin_amdgcn_readfirstlane(at) + __popcll(bal & ((1ull << lane) - 1ull));
+  if (take && at < most) list[at] = v;
+}
+
+// Marker list of active tile `slot`: entries k | d << kListShift for every
+// marker k whose stencil touches the tile, d = axis_from of its z (k < 2^24,
+// d < 16). Built once
+// per step, so that the spreading, whose planes spread over many workgroups,
+// starts from it instead of scanning the markers in each. NT threads test the
+// chunk boxes, then the markers of the chunks whose box meets the tile, and
+// collect the hits in LDS (kListLds of them; a longer list is found again and
+// written out directly). Order is arbitrary.
+constexpr int kListLds = 1024;
+// 28, not 24: of a marker index masked to 24 bits the compiler (ROCm 7.2) takes
+// the record's address as a 24-bit multiply, drops the mask, and then folds it
+// into a 32-bit multiply-add, which sees the bits above.
+constexpr int kListShift = 28;
+template <int NT>
+__device__ inline void list_item(const EnvView &e, const BodySet &bs, int slot, int tid) {
+  __shared__ int s_hit[kListLds], s_chunk[NT], s_n[3];  // [0] chunks, [1] hits, [2] first entry
+  constexpr int WAVES = NT / 64, PER = 4;               // chunks per wave in flight
+  const GridArgs &g = e.g;
+  const TileAt t = active_of(bs, slot);
+  const int x0 = t.x * 8, y0 = t.y * 8, z0 = t.z * 8;
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wx = min(8, g.nx - x0) + 3, wy = min(8, g.ny - y0) + 3, wz = min(8, g.nz - z0) + 3;
+  const int n = e.n, nchunks = (n + 63) >> 6;
+  int *out = s_hit;
+  int most = kListLds, cnt = 0;
+  for (int pass = 0; pass < 2; ++pass) {
+    if (tid < 2) s_n[tid] = 0;
+    __syncthreads();
+    for (int c0 = 0; c0 < nchunks; c0 += NT) {
+      const int cl = c0 + tid;
+      bool meets = false;
+      if (cl < nchunks) {
+        const gmem<int> *bp = (const gmem<int> *)bs.chunk_box + 4 * (size_t)cl;
+        const int4 box = make_int4(bp[0], bp[1], bp[2], bp[3]);
+        meets = box_hits(box.x, t.x) && box_hits(box.y, t.y) && box_hits(box.z, t.z);
+      }
+      wave_push(meets, cl, s_chunk, &s_n[0], NT, lane);
+      __syncthreads();
+      const int nc = __builtin_amdgcn_readfirstlane(s_n[0]);
+      for (int q0 = wv; q0 < nc; q0 += WAVES * PER) {
+        short4 base[PER];
+        int mk[PER];
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+          mk[r] = n;
+          if (q0 + r * WAVES < nc) {
+            mk[r] = s_chunk[q0 + r * WAVES] * 64 + lane;
+            const gmem<short> *mb = (const gmem<short> *)bs.mbase + 4 * (size_t)min(mk[r], n - 1);
+            base[r] = make_short4(mb[0], mb[1], mb[2], mb[3]);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+          if (q0 + r * WAVES >= nc) break;
+          const int d = axis_from(base[r].z, g.nz, z0);
+          const bool hit = mk[r] < n && axis_from(base[r].x, g.nx, x0) < wx && axis_from(base[r].y, g.ny, y0) < wy &&
+                           d < wz;
+          wave_push(hit, (int)((unsigned)mk[r] | ((unsigned)d << kListShift)), out, &s_n[1], most, lane);
+        }
+      }
+      __syncthreads();
+      if (tid == 0) s_n[0] = 0;
+      __syncthreads();
+    }
+    if (pass == 1) break;
+    cnt = s_n[1];
+    __syncthreads();
+    if (tid == 0) {
+      s_n[2] = cnt ? atomicAdd(&bs.counters[2], cnt) : 0;
+      gmem<int> *p = (gmem<int> *)bs.active + 4 * (size_t)slot;
+      p[2] = s_n[2];
+      p[3] = cnt;
+    }
+    __syncthreads();
+    out = e.list + s_n[2];
+    most = cnt;
+    if (cnt <= kListLds) {
+      for (int q = tid; q < cnt; q += NT) out[q] = s_hit[q];
+      break;
+    }
+  }
+  __syncthreads();  // the LDS arrays are reused by the next item
+}
+
 // ----------------------------------------------------------- band macros --
-// Density and unforced velocity u* (frame force, no IB force) of every cell
-// of active tile `slot`; also clears the tile's fixed-point immersed force.
-template <class S, bool ROT>
-__device__ inline void macro_item(const EnvView &e, const FrameF &fr, int cur, int slot, int tid) {
+// Density and unforced velocity u* (frame force, no immersed force) at node
+// (x, y, z) from the moments of its pulled deviations. Multiply-adds fuse
+// within one expression only, so that every kernel this is inlined into
+// rounds it the same way.
+template <bool ROT>
+__device__ inline vfloat4 macro_of(const FrameF &fr, float drho, float mx, float my, float mz, int x, int y, int z) {
+#pragma clang fp contract(on)
+  const float rho = 1.0f + drho;
+  float ax, ay, az;
+  frame_a0<ROT>(fr, (float)x, (float)y, (float)z, ax, ay, az);
+  float ux, uy, uz;
+  const float ir = 1.0f / rho;
+  solve_coriolis<ROT>(fr, mx * ir + 0.5f * ax, my * ir + 0.5f * ay, mz * ir + 0.5f * az, ux, uy, uz);
+  return vfloat4{rho, ux, uy, uz};
+}
+
+// macro_of cells of active tiles, NT a workgroup: item `item` is the
+// (item % (512 / NT))-th part of tile item / (512 / NT).
+template <int NT, class S, bool ROT>
+__device__ inline void macro_item(const EnvView &e, const BodySet &bs, const FrameF &fr, int cur, int item, int tid0) {
+  const int slot = item / (512 / NT), tid = item % (512 / NT) * NT + tid0;
   using T = typename S::T;
   const gmem<T> *__restrict__ src = (const gmem<T> *)e.f[cur];
   const GridArgs &g = e.g;
-  const int t = ((const gmem<int> *)e.active)[slot];
-  const int tx = t % g.tnx, ty = (t / g.tnx) % g.tny, tz = t / (g.tnx * g.tny);
-  const int x = tx * 8 + (tid & 7), y = ty * 8 + ((tid >> 3) & 7), z = tz * 8 + (tid >> 6);
-  float4 out = make_float4(1.f, 0.f, 0.f, 0.f);
+  const TileAt t = active_of(bs, slot);
+  const int x = t.x * 8 + (tid & 7), y = t.y * 8 + ((tid >> 3) & 7), z = t.z * 8 + (tid >> 6);
+  vfloat4 out = {1.f, 0.f, 0.f, 0.f};
   if (x < g.nx && y < g.ny && z < g.nz && (g.xper || (x > 0 && x < g.nx - 1))) {
     const int xm = g.xper ? wrap_idx(x - 1, g.nx) : x - 1;
     const int xp = g.xper ? wrap_idx(x + 1, g.nx) : x + 1;
@@ -309,97 +435,126 @@ __device__ inline void macro_item(const EnvView &e, const FrameF &fr, int cur, i
                     wrap_idx(z - 1, g.nz), z, wrap_idx(z + 1, g.nz), f);
     float drho, mx, my, mz;
     moments(f, drho, mx, my, mz);
-    const float rho = 1.0f + drho;
-    float ax, ay, az;
-    frame_a0<ROT>(fr, (float)x, (float)y, (float)z, ax, ay, az);
-    float ux, uy, uz;
-    const float ir = 1.0f / rho;
-    solve_coriolis<ROT>(fr, mx * ir + 0.5f * ax, my * ir + 0.5f * ay, mz * ir + 0.5f * az, ux, uy, uz);
-    out = make_float4(rho, ux, uy, uz);
+    out = macro_of<ROT>(fr, drho, mx, my, mz, x, y, z);
   }
-  ((gmem<vfloat4> *)e.macro)[(size_t)slot * 512 + tid] = vfloat4{out.x, out.y, out.z, out.w};
-  gmem<unsigned long long> *gp = (gmem<unsigned long long> *)e.gfix + (size_t)slot * 1536;
-  gp[tid] = 0ull;
-  gp[512 + tid] = 0ull;
-  gp[1024 + tid] = 0ull;
-  if (e.gcg != nullptr) {  // implicit correction: its search-direction force starts at zero too
-    gmem<unsigned long long> *gq = (gmem<unsigned long long> *)e.gcg + (size_t)slot * 1536;
-    gq[tid] = 0ull;
-    gq[512 + tid] = 0ull;
-    gq[1024 + tid] = 0ull;
-  }
+  ((gmem<vfloat4> *)e.macro)[(size_t)slot * 512 + tid] = out;
 }
 
 // --------------------------------------------------------- interpolation --
-// Markers 32*item .. 32*item+31, four per wave, 16 lanes each. Lane
-// sub = lane & 15 of a marker's group holds the x-row of stencil nodes
-// (0..3, sub & 3, sub >> 2): it issues the row's four gathers together, sums
-// the row, and a 16-lane butterfly (every lane of the group ends with the
-// same bits) completes the 64-node sums. Node weight delta = wx (wy wz),
-// the product the spreading uses.
 // pass 0: U*_k = sum u* delta, rho_k = sum rho delta, F_k = 2 alpha rho_k (U_k - U*_k).
 // pass p > 0 (multi-direct forcing): the interpolated velocity includes the
 // current immersed force, u = u* + (I + [omega]x)^-1 g / (2 rho), and
 // F_k += 2 alpha rho_k (U_k - U_k^interp).
 // The record carries this pass's F increment times dV (spreading adds each
-// pass into the step's force). With partials != nullptr: the fluid's force,
-// torque about the frame origin and power, summed per item into
-// partials[item][8].
+// pass into the step's force). With partials != nullptr: the marker's share of
+// the fluid's force, torque about the frame origin and power, partials[k][8].
+// Node weight delta = wx (wy wz), the product the spreading uses. The 64-node
+// sums add each x-row of four nodes in order, then the 16 rows by a butterfly,
+// in both forms below: the same bits.
+//   interp_item  (from the band macros) 16 lanes a marker, one x-row a lane;
+//   interp_wave  (from the populations) one wave a marker, one node a lane: no
+//                macro pass before it, for few markers.
+// Value of the lane N places on in its row of 16 (DPP rotation: a register
+// operand, where a shuffle goes through LDS). Where the values repeat with
+// period 2 N over the row (N = 8 always), that is the value of lane ^ N.
+template <int N>
+__device__ inline float row_turn(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xF, 0xF, true));
+}
+// Sum over each 16 lanes, the same bits in all of them: a butterfly of xors.
 __device__ inline float group16_sum(float v) {
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) v += shfl_xor_f(v, o);
+  v += row_turn<8>(v);
+  v += row_turn<4>(v);
+  v += row_turn<2>(v);
+  v += row_turn<1>(v);
   return v;
 }
 
-// Stencil geometry of marker position X for row lane sub: the base node per
-// axis, the four x weights, the row's y and z weights, and per x node of the
-// row its tile index and its cell index within the tile.
-struct StencilRow {
-  int base[3];
-  float wx[4], wy, wz;
-  int tile[4], lc[4];
-};
-
-__device__ inline StencilRow stencil_row(const GridArgs &g, const float X[3], int sub) {
-  StencilRow r;
-#pragma unroll
-  for (int ax = 0; ax < 3; ++ax) r.base[ax] = stencil_base(X[ax]);
-  const int jy = r.base[1] + (sub & 3), jz = r.base[2] + (sub >> 2);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) r.wx[i] = peskin4(X[0] - (float)(r.base[0] + i));
-  r.wy = peskin4(X[1] - (float)jy);
-  r.wz = peskin4(X[2] - (float)jz);
-  const int yn = wrap_idx(jy, g.ny), zn = wrap_idx(jz, g.nz);
-  const int trow = g.tnx * ((yn >> 3) + g.tny * (zn >> 3));
-  const int lrow = ((yn & 7) << 3) | ((zn & 7) << 6);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int xn = g.xper ? wrap_idx(r.base[0] + i, g.nx) : r.base[0] + i;
-    r.tile[i] = (xn >> 3) + trow;
-    r.lc[i] = (xn & 7) | lrow;
-  }
-  return r;
+// Value of lane `lane` of the wave.
+__device__ inline float lane_f(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(lane << 2, __float_as_int(v)));
 }
 
-template <bool ROT, bool MDF>
-__device__ inline void interp_item(const EnvView &e, const FrameF &fr, int item, int tid, float *partials) {
+// Stencil weights of a marker at X: lane q < 12 of the marker's lanes gets
+// the weight of node q & 3 on axis q >> 2 (one square root a lane instead of
+// six), the others a value nobody reads.
+__device__ inline float stencil_weight(const float X[3], const int base[3], int q) {
+  const int ax = min(q >> 2, 2);
+  const float x = ax == 0 ? X[0] : (ax == 1 ? X[1] : X[2]);
+  const int b = ax == 0 ? base[0] : (ax == 1 ? base[1] : base[2]);
+  return peskin4(x - (float)(b + (q & 3)));
+}
+
+// What one lane does with marker k's sums: force, record and wrench share
+// (the record's weights are stored by the caller).
+template <bool MDF>
+__device__ inline void force_marker(const EnvView &e, const BodySet &bs, const FrameF &fr, int k, float sr,
+                                    const float Ui[3], const float Xk[3], const float Uk[3], float dvk,
+                                    const int base[3], float *partials) {
   // multiply-adds fuse only within one expression, never across statements,
-  // so every kernel that inlines this item rounds its outputs identically
+  // so every kernel that inlines this rounds its outputs identically
 #pragma clang fp contract(on)
-  __shared__ float s_part[kInterpMk][8];
-  const int sub = tid & 15, mk = tid >> 4;
-  const int k = item * kInterpMk + mk;
+  const int n = e.n;
+  gmem<float> *F = (gmem<float> *)e.F, *mstate = (gmem<float> *)e.mstate;
+  gmem<float> *r = (gmem<float> *)e.rec + (size_t)k * REC;
+  float rk, Fk[3], inc[3];
+  // velocity to correct: U - U^interp, or on a slip wall its normal part
+  float dU[3] = {Uk[0] - Ui[0], Uk[1] - Ui[1], Uk[2] - Ui[2]};
+  if (e.slip) {
+    const float nk[3] = {bs.Nrm[k], bs.Nrm[n + k], bs.Nrm[2 * n + k]};
+    const float dn = dU[0] * nk[0] + dU[1] * nk[1] + dU[2] * nk[2];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) dU[c] = dn * nk[c];
+  }
+  if (!MDF) {
+    rk = sr;
+    mstate[k] = rk;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      mstate[(c + 1) * (size_t)n + k] = Ui[c];
+      inc[c] = e.alpha2 * rk * dU[c];
+      Fk[c] = inc[c];
+    }
+  } else {
+    rk = mstate[k];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      inc[c] = e.alpha2 * rk * dU[c];
+      Fk[c] = F[c * n + k] + inc[c];
+    }
+  }
+  float fd[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    F[c * n + k] = Fk[c];
+    fd[c] = Fk[c] * dvk;
+  }
+  *(gmem<vfloat4> *)(r + 12) = vfloat4{__int_as_float(base[0]), __int_as_float(base[1]), __int_as_float(base[2]), 0.f};
+  *(gmem<vfloat4> *)(r + 16) = vfloat4{inc[0] * dvk, inc[1] * dvk, inc[2] * dvk, 0.f};
+  if (partials == nullptr) return;
+  // fluid on body: -F dV; torque (X - x0) x (-F dV); power F.U dV
+  const float rx = Xk[0] - fr.org[0], ry = Xk[1] - fr.org[1], rz = Xk[2] - fr.org[2];
+  gmem<vfloat4> *p = (gmem<vfloat4> *)(partials + 8 * (size_t)k);
+  p[0] = vfloat4{-fd[0], -fd[1], -fd[2], -(ry * fd[2] - rz * fd[1])};
+  p[1] = vfloat4{-(rz * fd[0] - rx * fd[2]), -(rx * fd[1] - ry * fd[0]),
+                 fd[0] * Uk[0] + fd[1] * Uk[1] + fd[2] * Uk[2], 0.f};
+}
+
+// Markers NT / 16 a workgroup, from the band macros.
+template <int NT, bool ROT, bool MDF>
+__device__ inline void interp_item(const EnvView &e, const BodySet &bs, const FrameF &fr, int item, int tid,
+                                   float *partials) {
+#pragma clang fp contract(on)  // as force_marker
+  const int sub = tid & 15, lane = tid & 63;
+  const int k = item * (NT / 16) + (tid >> 4);
   const int n = e.n;
   const GridArgs &g = e.g;
   const bool live = k < n;
   // the environment's arrays through global pointers (see gmem)
-  const gmem<float> *X = (const gmem<float> *)e.X, *U = (const gmem<float> *)e.U;
-  const gmem<int> *tile_slot = (const gmem<int> *)e.tile_slot;
-  const gmem<vfloat4> *macro = (const gmem<vfloat4> *)e.macro;
-  gmem<float> *F = (gmem<float> *)e.F, *mstate = (gmem<float> *)e.mstate;
-  float part[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const gmem<float> *X = (const gmem<float> *)bs.X, *U = (const gmem<float> *)bs.U;
+  const gmem<int> *tile_slot = (const gmem<int> *)bs.tile_slot;
   float Xk[3] = {0.f, 0.f, 0.f}, Uk[3] = {0.f, 0.f, 0.f}, dvk = 0.f;
-  StencilRow st{};
+  int base[3] = {0, 0, 0};
   float sr = 0.f, sx = 0.f, sy = 0.f, sz = 0.f;
   if (live) {
 #pragma unroll
@@ -407,20 +562,35 @@ __device__ inline void interp_item(const EnvView &e, const FrameF &fr, int item,
       Xk[ax] = X[ax * n + k];
       // loaded now, used after the stencil gather: off the dependent chain
       Uk[ax] = U[ax * n + k];
+      base[ax] = stencil_base(Xk[ax]);
     }
     dvk = ((const gmem<float> *)e.dv)[k];
-    st = stencil_row(g, Xk, sub);
-    int sl[4];
+  }
+  // every lane takes part in the shuffles (a group of 16 is all live or all not)
+  const float w = stencil_weight(Xk, base, sub);
+  const int grp = lane & 48;
+  float wx[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) sl[i] = tile_slot[st.tile[i]];
-    float4 m[4];
+  for (int i = 0; i < 4; ++i) wx[i] = lane_f(w, grp + i);
+  const float wy = lane_f(w, grp + 4 + (sub & 3)), wz = lane_f(w, grp + 8 + (sub >> 2));
+  if (live) {
+    const int yn = wrap_idx(base[1] + (sub & 3), g.ny), zn = wrap_idx(base[2] + (sub >> 2), g.nz);
+    const int trow = g.tnx * ((yn >> 3) + g.tny * (zn >> 3));
+    const int lrow = ((yn & 7) << 3) | ((zn & 7) << 6);
+    int sl[4], lc[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      m[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (sl[i] >= 0) {
-        const vfloat4 v = macro[(size_t)sl[i] * 512 + st.lc[i]];
-        m[i] = make_float4(v.x, v.y, v.z, v.w);
-      } else
+      const int xn = g.xper ? wrap_idx(base[0] + i, g.nx) : base[0] + i;
+      sl[i] = tile_slot[(xn >> 3) + trow];
+      lc[i] = (xn & 7) | lrow;
+    }
+    vfloat4 m[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      m[i] = vfloat4{0.f, 0.f, 0.f, 0.f};
+      if (sl[i] >= 0)
+        m[i] = ((const gmem<vfloat4> *)e.macro)[(size_t)sl[i] * 512 + lc[i]];
+      else  // a tile beyond the capacity
         atomicOr(e.guard, (int)GUARD_CAPACITY);
     }
     if (MDF) {
@@ -430,105 +600,125 @@ __device__ inline void interp_item(const EnvView &e, const FrameF &fr, int item,
         const gmem<unsigned long long> *gp = (const gmem<unsigned long long> *)e.gfix + (size_t)sl[i] * 1536;
         const float h = 0.5f / m[i].x;
         float dx, dy, dz;
-        solve_coriolis<ROT>(fr, from_fix(gp[st.lc[i]]) * h, from_fix(gp[512 + st.lc[i]]) * h,
-                            from_fix(gp[1024 + st.lc[i]]) * h, dx, dy, dz);
+        solve_coriolis<ROT>(fr, from_fix(gp[lc[i]]) * h, from_fix(gp[512 + lc[i]]) * h, from_fix(gp[1024 + lc[i]]) * h,
+                            dx, dy, dz);
         m[i].y += dx;
         m[i].z += dy;
         m[i].w += dz;
       }
     }
-    const float wyz = st.wy * st.wz;
+    const float wyz = wy * wz;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float d = st.wx[i] * wyz;
+      const float d = wx[i] * wyz;
       sr += m[i].x * d;
       sx += m[i].y * d;
       sy += m[i].z * d;
       sz += m[i].w * d;
     }
   }
-  // every lane takes part (a group of 16 is all live or all not)
   sr = group16_sum(sr);
   sx = group16_sum(sx);
   sy = group16_sum(sy);
   sz = group16_sum(sz);
   if (live) {
-    gmem<float> *r = (gmem<float> *)e.rec + (size_t)k * REC;
-    if (sub == 0) *(gmem<vfloat4> *)r = vfloat4{st.wx[0], st.wx[1], st.wx[2], st.wx[3]};
-    if (sub < 4) r[4 + sub] = st.wy;                // row (sy, 0)
-    if ((sub & 3) == 0) r[8 + (sub >> 2)] = st.wz;  // row (0, sz)
-    if (sub == 0) {
-      float rk;
-      float Fk[3], inc[3];
-      const float Ui[3] = {sx, sy, sz};
-      // velocity to correct: U - U^interp, or on a slip wall its normal part
-      float dU[3] = {Uk[0] - Ui[0], Uk[1] - Ui[1], Uk[2] - Ui[2]};
-      if (e.slip) {
-        const float nk[3] = {e.Nrm[k], e.Nrm[n + k], e.Nrm[2 * n + k]};
-        const float dn = dU[0] * nk[0] + dU[1] * nk[1] + dU[2] * nk[2];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) dU[c] = dn * nk[c];
-      }
-      if (!MDF) {
-        rk = sr;
-        mstate[k] = rk;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          mstate[(c + 1) * (size_t)n + k] = Ui[c];
-          inc[c] = e.alpha2 * rk * dU[c];
-          Fk[c] = inc[c];
-        }
-      } else {
-        rk = mstate[k];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          inc[c] = e.alpha2 * rk * dU[c];
-          Fk[c] = F[c * n + k] + inc[c];
-        }
-      }
-      float fd[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        F[c * n + k] = Fk[c];
-        fd[c] = Fk[c] * dvk;
-        r[16 + c] = inc[c] * dvk;
-        r[12 + c] = __int_as_float(st.base[c]);
-      }
-      // fluid on body: -F dV; torque (X - x0) x (-F dV); power F.U dV
-      const float rx = Xk[0] - fr.org[0], ry = Xk[1] - fr.org[1], rz = Xk[2] - fr.org[2];
-      part[0] = -fd[0];
-      part[1] = -fd[1];
-      part[2] = -fd[2];
-      part[3] = -(ry * fd[2] - rz * fd[1]);
-      part[4] = -(rz * fd[0] - rx * fd[2]);
-      part[5] = -(rx * fd[1] - ry * fd[0]);
-      part[6] = fd[0] * Uk[0] + fd[1] * Uk[1] + fd[2] * Uk[2];
-    }
+    if (sub < 12) ((gmem<float> *)e.rec)[(size_t)k * REC + sub] = w;
+    const float Ui[3] = {sx, sy, sz};
+    if (sub == 0) force_marker<MDF>(e, bs, fr, k, sr, Ui, Xk, Uk, dvk, base, partials);
   }
-  if (partials == nullptr) return;  // uniform over the workgroup
-  if (sub == 0)
-    for (int q = 0; q < 7; ++q) s_part[mk][q] = part[q];
-  __syncthreads();
-  if (tid < 8) {
-    float sum = 0.f;
-    if (tid < 7)
-      for (int q = 0; q < kInterpMk; ++q) sum += s_part[q][tid];
-    partials[(size_t)item * 8 + tid] = sum;
-  }
-  __syncthreads();
 }
 
-__device__ __host__ inline int interp_items(int n) { return (n + kInterpMk - 1) / kInterpMk; }
+// Value of lane i of this lane's group of four (DPP quad permute).
+template <int I>
+__device__ inline float quad_lane(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), I * 0x55, 0xF, 0xF, true));
+}
+
+// Marker k by one wave (k uniform over it), first pass, straight from the
+// populations of buffer cur: lane = node (lane & 3, (lane >> 2) & 3, lane >> 4)
+// pulls its 27 populations and takes their moments, as macro_item does for the
+// cells of the band, so no macro pass goes before.
+template <class S, bool ROT>
+__device__ inline void interp_wave(const EnvView &e, const BodySet &bs, const FrameF &fr, int cur, int k, int lane,
+                                   float *partials) {
+#pragma clang fp contract(on)  // as force_marker
+  using T = typename S::T;
+  const gmem<T> *__restrict__ src = (const gmem<T> *)e.f[cur];
+  const GridArgs &g = e.g;
+  const int n = e.n;
+  const gmem<float> *X = (const gmem<float> *)bs.X, *U = (const gmem<float> *)bs.U;
+  float Xk[3], Uk[3];
+  int base[3];
+#pragma unroll
+  for (int ax = 0; ax < 3; ++ax) {
+    Xk[ax] = X[ax * n + k];
+    Uk[ax] = U[ax * n + k];
+    base[ax] = stencil_base(Xk[ax]);
+  }
+  const float dvk = ((const gmem<float> *)e.dv)[k];
+  const int x = g.xper ? wrap_idx(base[0] + (lane & 3), g.nx) : base[0] + (lane & 3);
+  const int y = wrap_idx(base[1] + ((lane >> 2) & 3), g.ny), z = wrap_idx(base[2] + (lane >> 4), g.nz);
+  const int sl = ((const gmem<int> *)bs.tile_slot)[(x >> 3) + g.tnx * ((y >> 3) + g.tny * (z >> 3))];
+  float f[Q];  // deviations h_i
+  pull27<S, true>(src, g, wrap_idx(x - 1, g.nx), x, wrap_idx(x + 1, g.nx), wrap_idx(y - 1, g.ny), y,
+                  wrap_idx(y + 1, g.ny), wrap_idx(z - 1, g.nz), z, wrap_idx(z + 1, g.nz), f);
+  // the weights while the populations are in flight
+  const float w = stencil_weight(Xk, base, lane);
+  const float wyz = lane_f(w, 4 + ((lane >> 2) & 3)) * lane_f(w, 8 + (lane >> 4));
+  const float d = lane_f(w, lane & 3) * wyz;
+  if (lane < 12) ((gmem<float> *)e.rec)[(size_t)k * REC + lane] = w;
+  float drho, mx, my, mz;
+  moments(f, drho, mx, my, mz);
+  vfloat4 m = macro_of<ROT>(fr, drho, mx, my, mz, x, y, z);
+  if (sl < 0) {  // a tile beyond the capacity
+    m = vfloat4{0.f, 0.f, 0.f, 0.f};
+    atomicOr(e.guard, (int)GUARD_CAPACITY);
+  }
+  float s[4] = {0.f, 0.f, 0.f, 0.f};
+  const float q[4] = {m.x, m.y, m.z, m.w};
+  const float d0 = quad_lane<0>(d), d1 = quad_lane<1>(d), d2 = quad_lane<2>(d), d3 = quad_lane<3>(d);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    s[c] += quad_lane<0>(q[c]) * d0;
+    s[c] += quad_lane<1>(q[c]) * d1;
+    s[c] += quad_lane<2>(q[c]) * d2;
+    s[c] += quad_lane<3>(q[c]) * d3;
+  }
+  // the 16 rows: lanes 4 apart, the butterfly of group16_sum
+#pragma unroll
+  for (int o = 32; o >= 16; o >>= 1)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) s[c] += shfl_xor_f(s[c], o);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    s[c] += row_turn<8>(s[c]);
+    s[c] += row_turn<4>(s[c]);
+  }
+  const float Ui[3] = {s[1], s[2], s[3]};
+  if (lane == 0) force_marker<false>(e, bs, fr, k, s[0], Ui, Xk, Uk, dvk, base, partials);
+}
+
+template <int NT = WG>
+__device__ __host__ inline int interp_items(int n) {
+  return (n + NT / 16 - 1) / (NT / 16);
+}
 __device__ __host__ inline int wave_items(int n) { return (n + kWavePer - 1) / kWavePer; }
 
-// Wrench of the step: the interpolation partials summed in item order.
-__device__ inline void wrench_sum(const float *__restrict__ partials, int nparts, float *__restrict__ wrench, int tid) {
+// Wrench of the step: the markers' shares in a fixed order by NT threads, as
+// WG / 8 interleaved sums whatever NT (so that every kernel gives the same
+// bits).
+template <int NT>
+__device__ inline void wrench_sum(const float *__restrict__ partials, int n, float *__restrict__ wrench, int tid) {
   __shared__ float s_red[WG];
-  const int col = tid & 7, row0 = tid >> 3;
-  float acc = 0.f;
-  if (col < 7)
-    for (int b = row0; b < nparts; b += WG / 8) acc += partials[(size_t)b * 8 + col];
-  s_red[tid] = acc;
+  for (int q = tid; q < WG; q += NT) {
+    const int col = q & 7;
+    float acc = 0.f;
+    if (col < 7) {
+#pragma unroll 8
+      for (int k = q >> 3; k < n; k += WG / 8) acc += ((const gmem<float> *)partials)[(size_t)k * 8 + col];
+    }
+    s_red[q] = acc;
+  }
   __syncthreads();
   if (tid < 8) {
     float sum = 0.f;
@@ -539,145 +729,156 @@ __device__ inline void wrench_sum(const float *__restrict__ partials, int nparts
 }
 
 // --------------------------------------------------------------- spreading --
-// Work item (active tile `slot`, part): g(x) = sum_k F_k dV_k delta(x - X_k)
-// over the tile's 512 cells. Wave w of part p owns marker chunks
-// c = 8 p + w (mod 8 kSpreadSplit), 64 markers each. It loads 64 of its chunk
-// boxes at once and keeps the chunks whose box meets the tile; in each such
-// chunk every lane tests its own marker and, on a hit, walks that marker's
-// 4x4x4 stencil, adding the nodes inside the tile into the LDS tile with
-// 64-bit LDS atomics (2^-40 fixed point). The workgroup then adds its nonzero
-// cells into the tile's fixed-point force, one global atomic per cell and
-// component. Integer sums make the result independent of every order.
+// The immersed force of one z-plane (64 cells) of an active tile per 256
+// threads: g(x) = sum_k F_k dV_k delta(x - X_k). The plane's markers are those
+// entries of the tile's list whose stencil has a node at this z; their records
+// are staged in LDS, kStage at a time, and taken by four lanes each, one lane
+// per x-row of the stencil in this plane, which adds the row's nodes inside the
+// tile into the plane's LDS cells with 64-bit LDS atomics (2^-40 fixed point).
+// Integer sums make the result independent of every order, and a plane belongs
+// to one workgroup, so its force is stored, or used from LDS, without global
+// atomics.
+// Planes, not tiles: the markers of a thin body crowd into few tiles (the
+// 128x64x64 fin has 32 active ones, with up to 579 of its 3,000 markers), and
+// the conversion to fixed point and the LDS atomics of one crowded tile on one
+// compute unit were the whole phase's time.
+constexpr int kStage = 256;  // marker records of a plane in LDS at a time
+
+template <int NC>
+struct alignas(16) SpreadLds {
+  unsigned long long acc[NC][64];
+  float wx[kStage][4], wy[kStage][4], v[kStage][NC];  // v: the spread values
+  float wz[kStage];
+  int bx[kStage], by[kStage];
+  int nhit;
+};
+
 __device__ inline void cg_direction(const EnvView &e, int k, const float *beta, bool first, float p[3]);
 
-// CG = true: the spread values are the search direction of the implicit
-// correction's conjugate-gradient step (cg_direction with beta, first), not
-// the record's.
-template <bool CG, int SPLIT = kSpreadSplit>
-__device__ inline void spread_item(const EnvView &e, int item, int tid, unsigned long long *target,
-                                   const float *beta = nullptr, bool first = true) {
-  __shared__ unsigned long long s_acc[3][512];
-  const int lane = tid & 63, wv = tid >> 6;
+// Plane `plane` of tile t by the 256 threads tid = 0 .. 255 (each 256 threads
+// of a larger workgroup take a plane of the same tile). The record's values
+// from FIRST on (NC of them) are spread; CG: instead the search direction of
+// the implicit correction's conjugate-gradient step (cg_direction with beta,
+// first). s.acc holds the start value (visible after the first barrier here);
+// a barrier ends the call.
+template <bool CG, int NC = 3, int FIRST = 16>
+__device__ inline void spread_plane(const EnvView &e, const BodySet &bs, const TileAt &t, int plane, int tid,
+                                    SpreadLds<NC> &s, const float *beta = nullptr, bool first = true) {
   const GridArgs &g = e.g;
+  const int x0 = t.x * 8, y0 = t.y * 8, lane = tid & 63;
   const int n = e.n;
-  const int nchunks = (n + 63) >> 6;
-  const int slot = item / SPLIT, part = item % SPLIT;
-  const int t = ((const gmem<int> *)e.active)[slot];
-  const int tx = t % g.tnx, ty = (t / g.tnx) % g.tny, tz = t / (g.tnx * g.tny);
-  for (int q = tid; q < 3 * 512; q += WG) (&s_acc[0][0])[q] = 0ull;
-  __syncthreads();
-  const int stride = (WG / 64) * SPLIT;
-  const int c_first = part * (WG / 64) + wv;
-  for (int it = 0; c_first + stride * 64 * it < nchunks; ++it) {
-    const int cl = c_first + stride * (lane + 64 * it);  // chunk examined by this lane
-    bool pass = false;
-    if (cl < nchunks) {
-      const gmem<int> *bp = (const gmem<int> *)e.chunk_box + 4 * (size_t)cl;
-      const int4 box = make_int4(bp[0], bp[1], bp[2], bp[3]);
-      pass = box_hits(box.x, tx) && box_hits(box.y, ty) && box_hits(box.z, tz);
-    }
-    unsigned long long cbal = __ballot(pass);
-    while (cbal) {
-      const int jc = __ffsll((long long)cbal) - 1;
-      cbal &= cbal - 1ull;
-      const int k = (c_first + stride * (jc + 64 * it)) * 64 + lane;
-      bool hit = false;
-      if (k < n) {
-        const gmem<short> *mb = (const gmem<short> *)e.mbase + 4 * (size_t)k;
-        const short4 b = make_short4(mb[0], mb[1], mb[2], mb[3]);
-        hit = axis_touches(b.x, g.nx, g.xper, tx) && axis_touches(b.y, g.ny, true, ty) &&
-              axis_touches(b.z, g.nz, true, tz);
-      }
-      if (hit) {
-        float r[20];
-        const gmem<vfloat4> *rp = (const gmem<vfloat4> *)e.rec + (size_t)k * (REC / 4);
-#pragma unroll
-        for (int q = 0; q < 5; ++q) {
-          const vfloat4 v = rp[q];
-          r[4 * q] = v.x;
-          r[4 * q + 1] = v.y;
-          r[4 * q + 2] = v.z;
-          r[4 * q + 3] = v.w;
-        }
-        if (CG) {
-          cg_direction(e, k, beta, first, &r[16]);
-          if (e.slip) {  // the search direction is a normal force p n
-            const float p0 = r[16];
-            r[16] = p0 * e.Nrm[k];
-            r[17] = p0 * e.Nrm[n + k];
-            r[18] = p0 * e.Nrm[2 * (size_t)n + k];
-          }
-        }
-        const int bx = __float_as_int(r[12]), by = __float_as_int(r[13]), bz = __float_as_int(r[14]);
-        int lx[4], ly[4], lz[4];  // local index part per stencil node, -1 outside the tile
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          int jx = bx + q, jy = wrap_idx(by + q, g.ny), jz = wrap_idx(bz + q, g.nz);
-          if (g.xper) jx = wrap_idx(jx, g.nx);
-          lx[q] = (jx >> 3) == tx ? (jx & 7) : -1;
-          ly[q] = (jy >> 3) == ty ? ((jy & 7) << 3) : -1;
-          lz[q] = (jz >> 3) == tz ? ((jz & 7) << 6) : -1;
-        }
-#pragma unroll
-        for (int qz = 0; qz < 4; ++qz) {
-          if (lz[qz] < 0) continue;
-#pragma unroll
-          for (int qy = 0; qy < 4; ++qy) {
-            if (ly[qy] < 0) continue;
-            const float wyz = r[4 + qy] * r[8 + qz];
-#pragma unroll
-            for (int qx = 0; qx < 4; ++qx) {
-              if (lx[qx] < 0) continue;
-              const float d = r[qx] * wyz;
-              const int lc = lx[qx] | ly[qy] | lz[qz];
-              atomicAdd(&s_acc[0][lc], to_fix(r[16] * d));
-              atomicAdd(&s_acc[1][lc], to_fix(r[17] * d));
-              atomicAdd(&s_acc[2][lc], to_fix(r[18] * d));
-            }
-          }
+  const gmem<int> *list = (const gmem<int> *)e.list + t.off;
+  int entry = tid < t.cnt ? list[tid] : 0;
+  for (int c0 = 0; c0 < t.cnt; c0 += kStage) {
+    if (tid == 0) s.nhit = 0;
+    __syncthreads();
+    const bool in = c0 + tid < t.cnt;
+    const int k = entry & ((1 << kListShift) - 1);
+    int sz = plane + 3 - (int)((unsigned)entry >> kListShift);  // the stencil node at this z, modulo nz
+    sz = sz < 0 ? sz + g.nz : (sz >= g.nz ? sz - g.nz : sz);
+    const bool hit = in && sz < 4;
+    if (c0 + kStage + tid < t.cnt) entry = list[c0 + kStage + tid];
+    const unsigned long long bal = __ballot(hit);
+    int at = 0;
+    if (lane == 0 && bal != 0ull) at = atomicAdd(&s.nhit, (int)__popcll(bal));
+    at = __builtin_amdgcn_readfirstlane(at) + __popcll(bal & ((1ull << lane) - 1ull));
+    if (hit) {
+      const gmem<vfloat4> *rp = (const gmem<vfloat4> *)e.rec + (size_t)k * (REC / 4);
+      const vfloat4 wx = rp[0], wy = rp[1], ba = rp[3], fd = rp[4];
+      const float wz = ((const gmem<float> *)rp)[8 + sz];
+      *(vfloat4 *)s.wx[at] = wx;
+      *(vfloat4 *)s.wy[at] = wy;
+      s.wz[at] = wz;
+      s.bx[at] = __float_as_int(ba.x);
+      s.by[at] = __float_as_int(ba.y);
+      float v[4] = {ba.w, fd.x, fd.y, fd.z};  // record values 15 .. 18
+      if (CG) {
+        cg_direction(e, k, beta, first, v + 1);
+        if (e.slip) {  // the search direction is a normal force p n
+          const float p0 = v[1];
+          v[1] = p0 * bs.Nrm[k];
+          v[2] = p0 * bs.Nrm[n + k];
+          v[3] = p0 * bs.Nrm[2 * (size_t)n + k];
         }
       }
+#pragma unroll
+      for (int c = 0; c < NC; ++c) s.v[at][c] = v[FIRST - 15 + c];
     }
+    __syncthreads();
+    const int m = s.nhit;
+    for (int j = tid >> 2; j < m; j += 64) {
+      const int ly = wrap_idx(s.by[j] + (lane & 3), g.ny) - y0;
+      if ((unsigned)ly >= 8u) continue;
+      const int bx = s.bx[j];
+      const float wyz = s.wy[j][lane & 3] * s.wz[j];
+      const vfloat4 wx = *(const vfloat4 *)s.wx[j];
+      float v[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) v[c] = s.v[j][c];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int lx = (g.xper ? wrap_idx(bx + i, g.nx) : bx + i) - x0;
+        if ((unsigned)lx >= 8u) continue;
+        const float d = wx[i] * wyz;
+        const int cell = lx | (ly << 3);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) atomicAdd(&s.acc[c][cell], to_fix(v[c] * d));
+      }
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  gmem<unsigned long long> *gp = (gmem<unsigned long long> *)target + (size_t)slot * 1536;
-  for (int q = tid; q < 3 * 512; q += WG) {
-    const unsigned long long v = (&s_acc[0][0])[q];
-    if (v != 0ull) __hip_atomic_fetch_add(&gp[q], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  __syncthreads();
+  if (t.cnt == 0) __syncthreads();
 }
 
-template <int SPLIT = kSpreadSplit>
-__device__ inline void spread_item(const EnvView &e, int item, int tid) {
-  spread_item<false, SPLIT>(e, item, tid, e.gfix);
+// Spreading items of NT threads per active tile: NT / 256 planes each.
+template <int NT>
+constexpr int kSpreadParts = 8 * 256 / NT;
+
+// Item `item` of the spreading into target (NC planes of 512 cells per slot);
+// add: on top of what it holds (the earlier passes of multi-direct forcing).
+template <int NT, bool CG, int NC = 3, int FIRST = 16>
+__device__ inline void spread_item(const EnvView &e, const BodySet &bs, int item, int tid, unsigned long long *target,
+                                   bool add, const float *beta = nullptr, bool first = true) {
+  __shared__ SpreadLds<NC> lds[NT / 256];
+  SpreadLds<NC> &s = lds[tid / 256];
+  const int slot = item / kSpreadParts<NT>, plane = item % kSpreadParts<NT> * (NT / 256) + tid / 256, lt = tid % 256;
+  gmem<unsigned long long> *gp = (gmem<unsigned long long> *)target + (size_t)slot * NC * 512 + plane * 64;
+  const TileAt t = active_of(bs, slot);
+  for (int q = lt; q < NC * 64; q += 256) (&s.acc[0][0])[q] = add ? gp[512 * (q >> 6) + (q & 63)] : 0ull;
+  spread_plane<CG, NC, FIRST>(e, bs, t, plane, lt, s, beta, first);
+  for (int q = lt; q < NC * 64; q += 256) gp[512 * (q >> 6) + (q & 63)] = (&s.acc[0][0])[q];
+  __syncthreads();
 }
 
 // ----------------------------------------------- single-lattice launches --
-__global__ void __launch_bounds__(WG) k_skin_mark(EnvView e, const float *pose) {
-  skin_item(e, pose, blockIdx.x, threadIdx.x);
+__global__ void __launch_bounds__(BT) k_skin_mark(EnvView e, const float *pose) {
+  skin_item<BT>(e, e.b[0], pose, blockIdx.x, threadIdx.x);
 }
 
-__global__ void __launch_bounds__(WG) k_active(EnvView e) { active_item(e, blockIdx.x, threadIdx.x); }
+__global__ void __launch_bounds__(WG) k_active(EnvView e) { active_item(e, e.b[0], blockIdx.x, threadIdx.x); }
 
 template <class S, bool ROT>
 __global__ void __launch_bounds__(WG) k_macro(EnvView e, FrameF fr, int cur) {
-  const XcdWalk w = xcd_walk(n_active_of(e));
-  for (int slot = w.first; slot < w.end; slot += w.step) macro_item<S, ROT>(e, fr, cur, slot, threadIdx.x);
+  const XcdWalk w = xcd_walk(n_active_of(e, e.b[0]));
+  for (int slot = w.first; slot < w.end; slot += w.step) {
+    list_item<WG>(e, e.b[0], slot, threadIdx.x);
+    macro_item<WG, S, ROT>(e, e.b[0], fr, cur, slot, threadIdx.x);
+  }
 }
 
-// Grid: exactly interp_items(n) workgroups. The markers of one XCD are
+// Grid: exactly interp_items<BT>(n) workgroups. The markers of one XCD are
 // consecutive, so its L2 holds the band macros of their stretch of body.
 template <bool ROT, bool MDF>
-__global__ void __launch_bounds__(WG) k_interp(EnvView e, FrameF fr, float *partials) {
-  interp_item<ROT, MDF>(e, fr, xcd_item(blockIdx.x, gridDim.x), threadIdx.x, partials);
+__global__ void __launch_bounds__(BT) k_interp(EnvView e, FrameF fr, float *partials) {
+  interp_item<BT, ROT, MDF>(e, e.b[0], fr, xcd_item(blockIdx.x, gridDim.x), threadIdx.x, partials);
 }
 
 // wrench != nullptr: workgroup 0 first sums the interpolation partials.
-__global__ void __launch_bounds__(WG) k_spread(EnvView e, float *wrench) {
-  if (blockIdx.x == 0 && wrench != nullptr) wrench_sum(e.partials, interp_items(e.n), wrench, threadIdx.x);
-  const int items = n_active_of(e) * kSpreadSplit;
-  for (int item = blockIdx.x; item < items; item += gridDim.x) spread_item(e, item, threadIdx.x);
+__global__ void __launch_bounds__(BT) k_spread(EnvView e, float *wrench, int add) {
+  if (blockIdx.x == 0 && wrench != nullptr) wrench_sum<BT>(e.partials, e.n, wrench, threadIdx.x);
+  const int items = kSpreadParts<BT> * n_active_of(e, e.b[0]);
+  for (int item = blockIdx.x; item < items; item += gridDim.x)
+    spread_item<BT, false>(e, e.b[0], item, threadIdx.x, e.gfix, add != 0);
 }
 
 // ------------------------------------------- implicit velocity correction --
@@ -704,8 +905,8 @@ __global__ void __launch_bounds__(WG) k_spread(EnvView e, float *wrench) {
 //     cg_apply_item  q = S p_j from gcg; stores p_j and q; p.q rows
 //     cg_update_item alpha_j = rz_j / p_j.q; G += alpha_j p_j; r -= alpha_j q;
 //                    rz_{j+1};
-//                    beta_{j+1} = rz_{j+1} / rz_j; clears gcg; on the last
-//                    step F = G / dV, the record carries G, wrench partials
+//                    beta_{j+1} = rz_{j+1} / rz_j; on the last step F = G / dV,
+//                    the record carries G, wrench partials
 //   then the ordinary spread of the record into gfix.
 // Each dot product is a sum of per-workgroup partial rows added in row order:
 // p.q by every update workgroup; r.z by the init or update workgroup that
@@ -805,13 +1006,13 @@ __device__ inline void cg_direction(const EnvView &e, int k, const float *beta, 
 }
 
 template <bool ROT>
-__device__ inline void cg_init_item(const EnvView &e, const FrameF &fr, int item) {
+__device__ inline void cg_init_item(const EnvView &e, const BodySet &bs, const FrameF &fr, int item) {
   const int n = e.n, k = item * kCgWG + (int)threadIdx.x;
   float rz[3] = {0.f, 0.f, 0.f};
   if (k < n) {
     float R[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) R[c] = e.U[c * n + k] - e.mstate[(c + 1) * (size_t)n + k];
+    for (int c = 0; c < 3; ++c) R[c] = bs.U[c * n + k] - e.mstate[(c + 1) * (size_t)n + k];
     float r[3] = {R[0], R[1], R[2]};
     if (ROT) {
       float wx, wy, wz;
@@ -821,7 +1022,7 @@ __device__ inline void cg_init_item(const EnvView &e, const FrameF &fr, int item
       r[2] += wz;
     }
     if (e.slip) {  // one unknown per marker, the normal force: r = n.(U - U*) in component 0
-      r[0] = e.Nrm[k] * R[0] + e.Nrm[n + k] * R[1] + e.Nrm[2 * (size_t)n + k] * R[2];
+      r[0] = bs.Nrm[k] * R[0] + bs.Nrm[n + k] * R[1] + bs.Nrm[2 * (size_t)n + k] * R[2];
       r[1] = r[2] = 0.f;
     }
     const float p2 = 2.0f * e.mstate[k];
@@ -834,7 +1035,7 @@ __device__ inline void cg_init_item(const EnvView &e, const FrameF &fr, int item
     }
   }
   cg_part3(rz, cg_rzp(e) + 4 * (size_t)item);
-  if (cg_last_arrival(e.counters + 1, cg_items(n))) {
+  if (cg_last_arrival(bs.counters + 1, cg_items(n))) {
     float t[3];
     cg_sum3(cg_rzp(e), cg_items(n), t);
     if (threadIdx.x < 3) cg_scal(e, 0, 0)[threadIdx.x] = t[threadIdx.x];
@@ -846,7 +1047,7 @@ __device__ inline void cg_init_item(const EnvView &e, const FrameF &fr, int item
 // gcg the spread of step j's search direction, which is stored here. The
 // weights are the record's, multiplied as the spreading multiplies them, so
 // the discrete S is symmetric.
-__device__ inline void cg_apply_item(const EnvView &e, int item, int tid, int j) {
+__device__ inline void cg_apply_item(const EnvView &e, const BodySet &bs, int item, int tid, int j) {
 #pragma clang fp contract(on)  // as interp_item
   __shared__ float s_pq[kInterpMk][3];
   const int sub = tid & 15, mk = tid >> 4;
@@ -868,7 +1069,7 @@ __device__ inline void cg_apply_item(const EnvView &e, int item, int tid, int j)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int xn = g.xper ? wrap_idx(bx + i, g.nx) : bx + i;
-      sl[i] = e.tile_slot[(xn >> 3) + trow];
+      sl[i] = bs.tile_slot[(xn >> 3) + trow];
       lc[i] = (xn & 7) | lrow;
     }
 #pragma unroll
@@ -885,7 +1086,7 @@ __device__ inline void cg_apply_item(const EnvView &e, int item, int tid, int j)
   if (live && sub == 0) {
     float q[3] = {qx, qy, qz};
     if (e.slip) {  // n . (S p n)
-      q[0] = e.Nrm[k] * qx + e.Nrm[n + k] * qy + e.Nrm[2 * (size_t)n + k] * qz;
+      q[0] = bs.Nrm[k] * qx + bs.Nrm[n + k] * qy + bs.Nrm[2 * (size_t)n + k] * qz;
       q[1] = q[2] = 0.f;
     }
     float p[3];
@@ -910,9 +1111,10 @@ __device__ inline void cg_apply_item(const EnvView &e, int item, int tid, int j)
 }
 
 // Step j of conjugate gradients for markers item*kCgWG ... On the last step
-// also the outputs: F = G / dV, the record's spread value G, and the wrench
-// partials per interpolation item (the layout wrench_sum reads).
-__device__ inline void cg_update_item(const EnvView &e, const FrameF &fr, int item, int j, bool last) {
+// also the outputs: F = G / dV, the record's spread value G, and the markers'
+// wrench shares.
+__device__ inline void cg_update_item(const EnvView &e, const BodySet &bs, const FrameF &fr, int item, int j,
+                                      bool last) {
 #pragma clang fp contract(on)  // as interp_item
   const int n = e.n, k = item * kCgWG + (int)threadIdx.x;
   float pq[3], alpha[3];
@@ -938,9 +1140,9 @@ __device__ inline void cg_update_item(const EnvView &e, const FrameF &fr, int it
     if (last) {
       if (e.slip) {  // the normal force gamma n
         const float gam = Gk[0];
-        Gk[0] = gam * e.Nrm[k];
-        Gk[1] = gam * e.Nrm[n + k];
-        Gk[2] = gam * e.Nrm[2 * (size_t)n + k];
+        Gk[0] = gam * bs.Nrm[k];
+        Gk[1] = gam * bs.Nrm[n + k];
+        Gk[2] = gam * bs.Nrm[2 * (size_t)n + k];
       }
       const float idv = 1.0f / e.dv[k];
       float *rec = e.rec + (size_t)k * REC;
@@ -949,8 +1151,8 @@ __device__ inline void cg_update_item(const EnvView &e, const FrameF &fr, int it
         e.F[c * n + k] = Gk[c] * idv;
         rec[16 + c] = Gk[c];
       }
-      const float Uk[3] = {e.U[k], e.U[n + k], e.U[2 * n + k]};
-      const float rx = e.X[k] - fr.org[0], ry = e.X[n + k] - fr.org[1], rzz = e.X[2 * n + k] - fr.org[2];
+      const float Uk[3] = {bs.U[k], bs.U[n + k], bs.U[2 * n + k]};
+      const float rx = bs.X[k] - fr.org[0], ry = bs.X[n + k] - fr.org[1], rzz = bs.X[2 * n + k] - fr.org[2];
       part[0] = -Gk[0];
       part[1] = -Gk[1];
       part[2] = -Gk[2];
@@ -962,7 +1164,7 @@ __device__ inline void cg_update_item(const EnvView &e, const FrameF &fr, int it
   }
   if (!last) {
     cg_part3(rzn, cg_rzp(e) + 4 * (size_t)item);
-    if (cg_last_arrival(e.counters + 1, cg_items(n))) {
+    if (cg_last_arrival(bs.counters + 1, cg_items(n))) {
       float t[3];
       cg_sum3(cg_rzp(e), cg_items(n), t);
       if (threadIdx.x < 3) {
@@ -973,41 +1175,33 @@ __device__ inline void cg_update_item(const EnvView &e, const FrameF &fr, int it
     }
     return;
   }
-  // groups of kInterpMk consecutive markers (aligned lanes of one wave) form
-  // one interpolation item
+  if (k < n) {
 #pragma unroll
-  for (int qd = 0; qd < 7; ++qd)
-    for (int o = kInterpMk / 2; o > 0; o >>= 1) part[qd] += shfl_xor_f(part[qd], o);
-  const int it = k / kInterpMk;
-  if ((k % kInterpMk) == 0 && k < n)
-#pragma unroll
-    for (int qd = 0; qd < 7; ++qd) e.partials[(size_t)it * 8 + qd] = part[qd];
+    for (int qd = 0; qd < 7; ++qd) e.partials[8 * (size_t)k + qd] = part[qd];
+  }
 }
 
 template <bool ROT>
-__global__ void __launch_bounds__(kCgWG) k_cg_init(EnvView e, FrameF fr) { cg_init_item<ROT>(e, fr, blockIdx.x); }
+__global__ void __launch_bounds__(kCgWG) k_cg_init(EnvView e, FrameF fr) {
+  cg_init_item<ROT>(e, e.b[0], fr, blockIdx.x);
+}
 
 // Spreading of step j's search direction into gcg.
-__global__ void __launch_bounds__(WG) k_spread_cg(EnvView e, int j) {
-  const int items = n_active_of(e) * kSpreadSplit;
+__global__ void __launch_bounds__(BT) k_spread_cg(EnvView e, int j) {
+  const int items = kSpreadParts<BT> * n_active_of(e, e.b[0]);
   const float *beta = cg_scal(e, 1, j);
   for (int item = blockIdx.x; item < items; item += gridDim.x)
-    spread_item<true>(e, item, threadIdx.x, e.gcg, beta, j == 0);
+    spread_item<BT, true>(e, e.b[0], item, threadIdx.x, e.gcg, false, beta, j == 0);
 }
 
 // Grid: exactly interp_items(n) workgroups (the last-arrival count).
 __global__ void __launch_bounds__(WG) k_cg_apply(EnvView e, int j) {
-  cg_apply_item(e, xcd_item(blockIdx.x, gridDim.x), threadIdx.x, j);
+  cg_apply_item(e, e.b[0], xcd_item(blockIdx.x, gridDim.x), threadIdx.x, j);
 }
 
-// Grid: at least cg_items(n) workgroups; the first cg_items(n) take the
-// markers, and all of them clear gcg for the next step's spread (not after
-// the last step: the next lattice step's macro pass clears it).
+// Grid: exactly cg_items(n) workgroups.
 __global__ void __launch_bounds__(kCgWG) k_cg_update(EnvView e, FrameF fr, int j, int last) {
-  if ((int)blockIdx.x < cg_items(e.n)) cg_update_item(e, fr, blockIdx.x, j, last != 0);
-  if (last) return;
-  const size_t words = (size_t)n_active_of(e) * 1536;
-  for (size_t q = (size_t)blockIdx.x * kCgWG + threadIdx.x; q < words; q += (size_t)gridDim.x * kCgWG) e.gcg[q] = 0ull;
+  cg_update_item(e, e.b[0], fr, blockIdx.x, j, last != 0);
 }
 
 // Block reduction of 8 floats over the workgroup.

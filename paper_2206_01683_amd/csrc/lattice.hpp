@@ -141,12 +141,15 @@ __device__ inline void solve_coriolis(const FrameF &fr, float bx, float by, floa
   uz = (bz - czv + wb * fr.omg[2]) * inv;
 }
 
-// Peskin's 4-point kernel on one axis, |r| <= 2.
+// Peskin's 4-point kernel on one axis, |r| <= 2. One square root for both
+// branches: lanes of a wave sit on either side of |r| = 1.
 __device__ inline float peskin4(float r) {
-  float a = fabsf(r);
-  if (a <= 1.0f) return 0.125f * (3.0f - 2.0f * a + __builtin_sqrtf(fmaxf(1.0f + 4.0f * a - 4.0f * a * a, 0.0f)));
-  if (a <= 2.0f) return 0.125f * (5.0f - 2.0f * a - __builtin_sqrtf(fmaxf(-7.0f + 12.0f * a - 4.0f * a * a, 0.0f)));
-  return 0.0f;
+  const float a = fabsf(r);
+  const bool near = a <= 1.0f;
+  const float q = near ? 1.0f + 4.0f * a - 4.0f * a * a : -7.0f + 12.0f * a - 4.0f * a * a;
+  const float s = __builtin_sqrtf(fmaxf(q, 0.0f));
+  const float v = near ? 0.125f * (3.0f - 2.0f * a + s) : 0.125f * (5.0f - 2.0f * a - s);
+  return a <= 2.0f ? v : 0.0f;
 }
 
 __device__ inline int wrap_idx(int j, int n) {
@@ -155,6 +158,6 @@ __device__ inline int wrap_idx(int j, int n) {
 }
 
 // Device guard bits
-enum : int { GUARD_UNSTABLE = 1, GUARD_MARKER_RANGE = 2, GUARD_CAPACITY = 4, GUARD_BONE = 8, GUARD_SCHEDULE = 16 };
+enum : int { GUARD_UNSTABLE = 1, GUARD_MARKER_RANGE = 2, GUARD_CAPACITY = 4, GUARD_BONE = 8 };
 
 }  // namespace lbmib

@@ -30,12 +30,12 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Workspace layout (all offsets 256-byte aligned).
 struct Layout {
-  size_t sched;             // scheduling words of the overlapped step
   int tnx, tny, tnz, ntiles, cap, maxm;
-  size_t guard, counters, tile_flag, tile_slot, tile_slot2, active, mbase, chunk_box, partials, macro, gbuf, rec, mstate;
+  size_t guard, tile_flag, list, partials, macro, gbuf, rec, mstate;
+  size_t counters[2], tile_slot[2], active[2], mbase[2], chunk_box[2], nrm[2];  // the two body sets (nrm: slip only)
+  size_t X2, U2;            // marker arrays of the second set; the first set's are the caller's
   size_t gbar, adjfix, mbar, pbar, facebuf;
   size_t gcg, cg, cgpart;  // implicit velocity correction only
-  size_t nrm;              // slip walls only
   size_t total;
 };
 
@@ -93,6 +93,11 @@ void pop_strides(const lbm_params *p, uint32_t &ps, uint32_t &rs) {
   }
 }
 
+// Marker list entries per marker: the most tiles a stencil touches.
+size_t list_entries(const lbm_params *p) {
+  return (size_t)axis_tiles_most(p->nx) * axis_tiles_most(p->ny) * axis_tiles_most(p->nz);
+}
+
 Layout layout(const lbm_params *p) {
   Layout L{};
   L.tnx = (p->nx + 7) / 8;
@@ -111,15 +116,18 @@ Layout layout(const lbm_params *p) {
     return at;
   };
   L.guard = take(64);
-  L.counters = take(64);
-  L.sched = take(sizeof(unsigned) * SCHED_WORDS);
   L.tile_flag = take(sizeof(int) * L.ntiles);
-  L.tile_slot = take(sizeof(int) * L.ntiles);
-  L.tile_slot2 = take(sizeof(int) * L.ntiles);  // the one-launch step's second tile map
-  L.active = take(sizeof(int) * L.cap);
-  L.mbase = take(sizeof(short4) * (size_t)L.maxm);
-  L.chunk_box = take(sizeof(int4) * (size_t)((L.maxm + 63) / 64 + 8));
-  L.partials = take(sizeof(float) * 8 * (size_t)interp_items(L.maxm));
+  for (int q = 0; q < 2; ++q) {
+    L.counters[q] = take(64);
+    L.tile_slot[q] = take(sizeof(int) * L.ntiles);
+    L.active[q] = take(sizeof(int4) * L.cap);
+    L.mbase[q] = take(sizeof(short4) * (size_t)L.maxm);
+    L.chunk_box[q] = take(sizeof(int4) * (size_t)((L.maxm + 63) / 64 + 8));
+  }
+  L.X2 = take(sizeof(float) * 3 * (size_t)L.maxm);
+  L.U2 = take(sizeof(float) * 3 * (size_t)L.maxm);
+  L.list = take(sizeof(int) * list_entries(p) * (size_t)L.maxm);
+  L.partials = take(sizeof(float) * 8 * (size_t)L.maxm);
   L.macro = take(sizeof(float) * 4 * 512 * (size_t)L.cap);
   L.gbuf = take(sizeof(unsigned long long) * 3 * 512 * (size_t)L.cap);
   L.rec = take(sizeof(float) * REC * (size_t)L.maxm);
@@ -132,7 +140,7 @@ Layout layout(const lbm_params *p) {
     L.pbar = take(sizeof(float) * 24 * kPoseSplit * (size_t)p->max_bones);
     L.facebuf = take(sizeof(float) * 2 * 4 * (size_t)p->ny * p->nz);
   }
-  L.nrm = p->wall_mode == LBM_WALL_SLIP ? take(sizeof(float) * 3 * (size_t)L.maxm) : 0;
+  for (int q = 0; q < 2; ++q) L.nrm[q] = p->wall_mode == LBM_WALL_SLIP ? take(sizeof(float) * 3 * (size_t)L.maxm) : 0;
   L.gcg = L.cg = L.cgpart = 0;
   if (p->ib_scheme == LBM_IB_IMPLICIT) {
     L.gcg = take(sizeof(unsigned long long) * 3 * 512 * (size_t)L.cap);
@@ -141,6 +149,25 @@ Layout layout(const lbm_params *p) {
   }
   L.total = o;
   return L;
+}
+
+// Workspace bytes that count against LBM_STATIC_WORKSPACE_BYTES: tiles, markers
+// and what the options ask for, without the second body set, the marker
+// lists and the markers' wrench shares (whose room the static array has beside
+// that limit).
+size_t static_need(const lbm_params *p) {
+  const Layout L = layout(p);
+  const size_t m = L.maxm, nt = L.ntiles, cap = L.cap;
+  const auto up = [](size_t v) { return align_up(v, 256); };
+  size_t o = 3 * 256;
+  o += 3 * up(4 * nt) + up(4 * cap) + up(8 * m) + up(16 * ((m + 63) / 64 + 8)) + up(32 * (size_t)interp_items(L.maxm));
+  o += up(8192 * cap) + up(12288 * cap) + up(sizeof(float) * REC * m) + up(16 * m);
+  if (p->with_adjoint)
+    o += up(6144 * cap) + up(16384 * cap) + up(24 * m) + up(sizeof(float) * 24 * kPoseSplit * (size_t)p->max_bones) +
+         up(32 * (size_t)p->ny * p->nz);
+  if (p->wall_mode == LBM_WALL_SLIP) o += up(12 * m);
+  if (p->ib_scheme == LBM_IB_IMPLICIT) o += up(12288 * cap) + up(48 * m) + up(sizeof(float) * cg_part_floats(L.maxm));
+  return o;
 }
 
 __global__ void k_fill_int(int *p, int v, int n) {
@@ -276,23 +303,28 @@ EnvView env_view(lbm_ctx *c, const lbm_markers *m) {
     e.weight = m->weight;
     e.dv = m->dv;
     e.bone = m->bone;
-    e.X = m->X;
-    e.U = m->U;
     e.F = m->F;
     if (c->p.wall_mode == LBM_WALL_SLIP) {
       e.slip = 1;
       e.nrest = m->nrest;
-      e.Nrm = wsp<float>(c, c->L.nrm);
     }
   }
+  for (int q = 0; q < 2; ++q) {
+    BodySet &bs = e.b[q];
+    if (e.ib) {
+      bs.X = q == 0 ? m->X : wsp<float>(c, c->L.X2);
+      bs.U = q == 0 ? m->U : wsp<float>(c, c->L.U2);
+      if (e.slip) bs.Nrm = wsp<float>(c, c->L.nrm[q]);
+    }
+    bs.tile_slot = wsp<int>(c, c->L.tile_slot[q]);
+    bs.mbase = wsp<short4>(c, c->L.mbase[q]);
+    bs.chunk_box = wsp<int4>(c, c->L.chunk_box[q]);
+    bs.active = wsp<int4>(c, c->L.active[q]);
+    bs.counters = wsp<int>(c, c->L.counters[q]);
+  }
   e.tile_flag = wsp<int>(c, c->L.tile_flag);
-  e.tile_slot = wsp<int>(c, c->L.tile_slot);
-  e.active = wsp<int>(c, c->L.active);
-  e.counters = wsp<int>(c, c->L.counters);
+  e.list = wsp<int>(c, c->L.list);
   e.guard = wsp<int>(c, c->L.guard);
-  e.sched = wsp<unsigned>(c, c->L.sched);
-  e.mbase = wsp<short4>(c, c->L.mbase);
-  e.chunk_box = wsp<int4>(c, c->L.chunk_box);
   e.partials = wsp<float>(c, c->L.partials);
   e.macro = wsp<float4>(c, c->L.macro);
   e.gfix = wsp<unsigned long long>(c, c->L.gbuf);
@@ -362,90 +394,82 @@ lbm_status launch_collide(lbm_ctx *c, const EnvView &e, const FrameF &fr, bool r
   return launched();
 }
 
-// Workgroups of `kernel` (WG threads) that the current device holds at once,
-// or 0 if the runtime cannot tell.
-template <class K>
-int coresident_workgroups(K kernel) {
-  int dev = 0, cus = 0, per_cu = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
-                                              hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, WG, 0) != hipSuccess)
-    return 0;
-  return per_cu * cus;
-}
+// The marker phases beside the collide (step.hpp) unless ib_workgroups = -1 asks
+// for every phase in a launch of its own before it. Steps in launches of their
+// own against beside: 64x32x32 sphere 36.4, 15.8 us; 128x64x64 fin 57.4, 36.0;
+// 150x50x100 two fish 93.1 (54 with linear collide blocks), 54.0; 384x192x192
+// fish 570, 526, in FP16 300, 291.
+bool beside_collide(const lbm_ctx *c) { return c->p.ib_workgroups >= 0; }
 
-// The chain's barrier needs all its workgroups resident together: nib is
-// held to what the device holds at once of this kernel (queried once per
-// form; the results do not depend on nib).
-template <class S, bool TRT>
-lbm_status step_overlap_kernels(const EnvView &e, const FrameF &fr, int cur, int nib, int passes, float *wrench,
-                                const float *next_pose, int *next_slots, hipStream_t s, bool xper, bool rot,
-                                bool yz) {
-#define LBM_STEP_OVERLAP(XP, RT, YZ_)                                                                           \
-  do {                                                                                                          \
-    static const int cap = coresident_workgroups(k_step_overlap<S, XP, RT, YZ_, TRT>);                          \
-    const int n = std::min(nib, cap);                                                                           \
-    if (n < 1) return LBM_ERR_DEVICE;                                                                           \
-    k_step_overlap<S, XP, RT, YZ_, TRT><<<n + e.nblocks, WG, 0, s>>>(e, fr, cur, n, passes, wrench, next_pose,  \
-                                                                    next_slots);                                \
+// Launches the form of KERNEL for (S, e, rot, TRT) with LBM_STEP_ARGS.
+#define LBM_STEP_FORM(KERNEL, ...)                                                          \
+  do {                                                                                      \
+    const bool yz_ = !(e.g.yper && e.g.zper), xper_ = e.g.xper != 0;                        \
+    if (yz_) {                                                                              \
+      if (xper_ && rot) KERNEL<S, true, true, true, TRT><<<__VA_ARGS__>>> LBM_STEP_ARGS;    \
+      else if (xper_) KERNEL<S, true, false, true, TRT><<<__VA_ARGS__>>> LBM_STEP_ARGS;     \
+      else if (rot) KERNEL<S, false, true, true, TRT><<<__VA_ARGS__>>> LBM_STEP_ARGS;       \
+      else KERNEL<S, false, false, true, TRT><<<__VA_ARGS__>>> LBM_STEP_ARGS;               \
+    } else if (xper_ && rot) {                                                              \
+      KERNEL<S, true, true, false, TRT><<<__VA_ARGS__>>> LBM_STEP_ARGS;                     \
+    } else if (xper_) {                                                                     \
+      KERNEL<S, true, false, false, TRT><<<__VA_ARGS__>>> LBM_STEP_ARGS;                    \
+    } else if (rot) {                                                                       \
+      KERNEL<S, false, true, false, TRT><<<__VA_ARGS__>>> LBM_STEP_ARGS;                    \
+    } else {                                                                                \
+      KERNEL<S, false, false, false, TRT><<<__VA_ARGS__>>> LBM_STEP_ARGS;                   \
+    }                                                                                       \
   } while (0)
-  if (yz) {  // open y or z faces
-    if (xper && rot)
-      LBM_STEP_OVERLAP(true, true, true);
-    else if (xper)
-      LBM_STEP_OVERLAP(true, false, true);
-    else if (rot)
-      LBM_STEP_OVERLAP(false, true, true);
-    else
-      LBM_STEP_OVERLAP(false, false, true);
-  } else if (xper && rot) {
-    LBM_STEP_OVERLAP(true, true, false);
-  } else if (xper) {
-    LBM_STEP_OVERLAP(true, false, false);
-  } else if (rot) {
-    LBM_STEP_OVERLAP(false, true, false);
-  } else {
-    LBM_STEP_OVERLAP(false, false, false);
-  }
-#undef LBM_STEP_OVERLAP
-  return launched();
-}
 
-// Whether the immersed-boundary chain runs beside the collide, one launch per
-// step: on request only (ib_workgroups > 0 chain workgroups, direct forcing).
-// Under the collide's load the chain's dependent accesses slow several-fold,
-// so it pays only where the collide is long enough to hide it. On the
-// 384x192x192 fish at F32 with 24-40 chain workgroups a step takes
-// 0.532-0.543 ms against 0.570 ms in separate launches (fewer than 20 and the
-// chain outlasts the collide; more take slots from it); with 2-byte storage
-// (the collide takes 255 us, the chain longer), four forcing passes, or
-// lattices small for their markers (the 150x50x100 two-fish domain, the
-// 128x64x64 fin) it loses.
-bool overlap_chain(const lbm_ctx *c) { return c->p.ib_scheme == LBM_IB_DIRECT && c->p.ib_workgroups > 0; }
-
-// The band macros, interpolation and spreading beside the collide, and the
-// next step's skinning and binning (next_pose != null) into next_slots, in one
-// launch (k_step_overlap) with e0.tile_slot this step's tile map; the collide
-// blocks take 512 cells each (the context's 2-D shape if it has 512 cells,
-// else 512 consecutive cells).
+// The shape of one launch of a step: marker workgroups, bulk blocks from
+// first_bulk on, spacing and LDS reservation (see kGap); lds_own: the kernel's
+// own LDS.
+struct StepLaunch {
+  int first_bulk, gap, grid;
+  size_t lds;
+};
 template <class S>
-lbm_status launch_step_overlap(lbm_ctx *c, const EnvView &e0, const FrameF &fr, bool rot, float *wrench,
-                               const float *next_pose, int *next_slots) {
-  EnvView e = e0;
-  if (!(c->by > 0 && c->bx * c->by == WG)) {
-    e.bx = WG;
-    e.by = 0;
-    e.gx = e.gy = 0;
-    e.nblocks = (int)(((size_t)c->p.nx * c->p.ny * c->p.nz + WG - 1) / WG);
-  }
-  const int nib = c->p.ib_workgroups;
-  const bool yz = !(e.g.yper && e.g.zper), xper = e.g.xper != 0;
-  if (c->p.collision == LBM_COLLIDE_TRT)
-    return step_overlap_kernels<S, true>(e, fr, c->cur, nib, c->p.mdf_iters, wrench, next_pose, next_slots,
-                                         c->stream, xper, rot, yz);
-  return step_overlap_kernels<S, false>(e, fr, c->cur, nib, c->p.mdf_iters, wrench, next_pose, next_slots, c->stream,
-                                        xper, rot, yz);
+StepLaunch step_launch(const EnvView &e, int front, int first_bulk, int bulk, size_t lds_own) {
+  const int groups = (front + 7) / 8;
+  const bool cap = S::kind == StoreF32::kind && bulk_blocks(e) >= kCapBlocks;
+  const size_t want = collide_lds<S>(dim3(BT));
+  const int gap = cap && bulk > 8 * kCapResident ? std::min(kGap, bulk / std::max(1, groups)) : 0;
+  return {first_bulk, gap, 8 * groups + bulk, cap && want > lds_own ? want - lds_own : 0};
 }
+
+template <class S, bool TRT>
+void step_macro_kernels(const EnvView &e, const FrameF &fr, int cur, bool rot, int nl, NextStep next, int bulk,
+                        hipStream_t s) {
+  const int nm = std::min(2 * e.cap, kMacroWorkgroups);
+  const StepLaunch l = step_launch<S>(e, nm + nl + (next.pose ? skin_items<BT>(e.n) : 0), 0, bulk, 5 * 1024);
+#define LBM_STEP_ARGS (e, fr, cur, nm, nl, next, l.gap)
+  LBM_STEP_FORM(k_step_macro, l.grid, BT, l.lds, s);
+#undef LBM_STEP_ARGS
+}
+
+// nl: workgroups for the marker lists, 0 after k_step_macro.
+template <class S, bool TRT>
+void step_interp_kernels(const EnvView &e, const FrameF &fr, int cur, bool rot, int nl, float *partials, NextStep next,
+                         int first_bulk, int bulk, hipStream_t s) {
+  const int front = nl > 0 ? (e.n + kStepMk - 1) / kStepMk + nl + (next.pose ? skin_items<BT>(e.n) : 0)
+                           : interp_items<BT>(e.n);
+  const StepLaunch l = step_launch<S>(e, front, first_bulk, bulk, 5 * 1024);
+#define LBM_STEP_ARGS (e, fr, cur, nl, partials, next, l.first_bulk, l.gap)
+  LBM_STEP_FORM(k_step_interp, l.grid, BT, l.lds, s);
+#undef LBM_STEP_ARGS
+}
+
+template <class S, bool TRT>
+void step_band_kernels(const EnvView &e, const FrameF &fr, int cur, bool rot, int add, float *wrench, NextStep next,
+                       int first_bulk, hipStream_t s) {
+  const int nt = std::min(8 * e.cap, kBandWorkgroups);
+  const StepLaunch l = step_launch<S>(e, nt + (wrench ? 1 : 0) + (next.pose ? active_items<BT>(e) : 0), first_bulk,
+                                      bulk_blocks(e) - first_bulk, sizeof(SpreadLds<3>) + 2 * 1024);
+#define LBM_STEP_ARGS (e, fr, cur, nt, add, wrench, next, l.first_bulk, l.gap)
+  LBM_STEP_FORM(k_step_band, l.grid, BT, l.lds, s);
+#undef LBM_STEP_ARGS
+}
+#undef LBM_STEP_FORM
 
 template <class S>
 lbm_status launch_macro(lbm_ctx *c, const EnvView &e, const FrameF &fr, bool rot) {
@@ -458,23 +482,23 @@ lbm_status launch_macro(lbm_ctx *c, const EnvView &e, const FrameF &fr, bool rot
 }
 
 // wrench != nullptr: also sum the interpolation kernel's wrench partials.
-lbm_status launch_spread(lbm_ctx *c, const EnvView &e, float *wrench) {
-  const int grid = std::min(c->L.cap * kSpreadSplit, 2048);
-  k_spread<<<grid, WG, 0, c->stream>>>(e, wrench);
+// add: on top of the earlier forcing passes' force.
+lbm_status launch_spread(lbm_ctx *c, const EnvView &e, float *wrench, bool add) {
+  k_spread<<<std::min(kSpreadParts<BT> * c->L.cap, 2048), BT, 0, c->stream>>>(e, wrench, add ? 1 : 0);
   return launched();
 }
 
 lbm_status launch_interp(lbm_ctx *c, const EnvView &e, const FrameF &fr, bool rot, bool mdf, bool want_wrench) {
-  const int grid = interp_items(e.n);
+  const int grid = interp_items<BT>(e.n);
   float *part = want_wrench ? e.partials : nullptr;
   if (rot && mdf)
-    k_interp<true, true><<<grid, WG, 0, c->stream>>>(e, fr, part);
+    k_interp<true, true><<<grid, BT, 0, c->stream>>>(e, fr, part);
   else if (rot)
-    k_interp<true, false><<<grid, WG, 0, c->stream>>>(e, fr, part);
+    k_interp<true, false><<<grid, BT, 0, c->stream>>>(e, fr, part);
   else if (mdf)
-    k_interp<false, true><<<grid, WG, 0, c->stream>>>(e, fr, part);
+    k_interp<false, true><<<grid, BT, 0, c->stream>>>(e, fr, part);
   else
-    k_interp<false, false><<<grid, WG, 0, c->stream>>>(e, fr, part);
+    k_interp<false, false><<<grid, BT, 0, c->stream>>>(e, fr, part);
   return launched();
 }
 
@@ -488,16 +512,15 @@ lbm_status launch_implicit(lbm_ctx *c, const EnvView &e, const FrameF &fr, bool 
   else
     k_cg_init<false><<<items, kCgWG, 0, c->stream>>>(e, fr);
   if ((st = launched()) != LBM_OK) return st;
-  const int spread_grid = std::min(c->L.cap * kSpreadSplit, 2048);
-  const int clear_grid = std::max(items, std::min((int)(((size_t)c->L.cap * 1536 + 4 * kCgWG - 1) / (4 * kCgWG)), 1024));
+  const int spread_grid = std::min(kSpreadParts<BT> * c->L.cap, 2048);
   const int steps = c->p.mdf_iters;
   for (int j = 0; j < steps; ++j) {
     const bool last = j == steps - 1;
-    k_spread_cg<<<spread_grid, WG, 0, c->stream>>>(e, j);
+    k_spread_cg<<<spread_grid, BT, 0, c->stream>>>(e, j);
     if ((st = launched()) != LBM_OK) return st;
     k_cg_apply<<<interp_items(e.n), WG, 0, c->stream>>>(e, j);
     if ((st = launched()) != LBM_OK) return st;
-    k_cg_update<<<last ? items : clear_grid, kCgWG, 0, c->stream>>>(e, fr, j, last ? 1 : 0);
+    k_cg_update<<<items, kCgWG, 0, c->stream>>>(e, fr, j, last ? 1 : 0);
     if ((st = launched()) != LBM_OK) return st;
   }
   return LBM_OK;
@@ -514,6 +537,23 @@ void prof_step(lbm_ctx *c, bool chained) {
   c->prof_used++;
 }
 
+// The forcing passes of one step from its band macros, up to the last spread
+// (which the caller does, on top of the force if passes > 1).
+lbm_status launch_passes(lbm_ctx *c, const EnvView &e, const FrameF &fr, bool rot, bool want_wrench) {
+  lbm_status st;
+  if (c->p.ib_scheme == LBM_IB_IMPLICIT) {
+    if ((st = launch_interp(c, e, fr, rot, false, false)) != LBM_OK) return st;
+    return launch_implicit(c, e, fr, rot);
+  }
+  const int passes = c->p.mdf_iters;
+  for (int it = 0; it < passes; ++it) {
+    if (it > 0 && (st = launch_spread(c, e, nullptr, it > 1)) != LBM_OK) return st;
+    if ((st = launch_interp(c, e, fr, rot, it > 0, want_wrench && it == passes - 1)) != LBM_OK) return st;
+  }
+  return LBM_OK;
+}
+bool spread_adds(const lbm_ctx *c) { return c->p.ib_scheme == LBM_IB_DIRECT && c->p.mdf_iters > 1; }
+
 template <class S>
 lbm_status step_one(lbm_ctx *c, const lbm_markers *m, const float *pose, const lbm_frame *frame, float *wrench) {
   const FrameF fr = frame_f(frame);
@@ -522,26 +562,17 @@ lbm_status step_one(lbm_ctx *c, const lbm_markers *m, const float *pose, const l
   lbm_status st;
   prof_mark(c, 0);
   if (e.ib) {
-    k_skin_mark<<<skin_items(e.n), WG, 0, c->stream>>>(e, pose);
+    k_skin_mark<<<skin_items<BT>(e.n), BT, 0, c->stream>>>(e, pose);
     if ((st = launched()) != LBM_OK) return st;
-    k_active<<<(e.ntiles + WG - 1) / WG, WG, 0, c->stream>>>(e);
+    k_active<<<active_items(e), WG, 0, c->stream>>>(e);
     if ((st = launched()) != LBM_OK) return st;
     c->slots_dirty = true;
     if ((st = launch_macro<S>(c, e, fr, rot)) != LBM_OK) return st;
-    const int passes = c->p.mdf_iters;
-    if (c->p.ib_scheme == LBM_IB_IMPLICIT) {
-      if ((st = launch_interp(c, e, fr, rot, false, false)) != LBM_OK) return st;
-      if ((st = launch_implicit(c, e, fr, rot)) != LBM_OK) return st;
-    } else {
-      for (int it = 0; it < passes; ++it) {
-        if (it > 0 && (st = launch_spread(c, e, nullptr)) != LBM_OK) return st;
-        if ((st = launch_interp(c, e, fr, rot, it > 0, wrench != nullptr && it == passes - 1)) != LBM_OK) return st;
-      }
-    }
-    if ((st = launch_spread(c, e, wrench)) != LBM_OK) return st;
+    if ((st = launch_passes(c, e, fr, rot, wrench != nullptr)) != LBM_OK) return st;
+    if ((st = launch_spread(c, e, wrench, spread_adds(c))) != LBM_OK) return st;
   } else if (c->slots_dirty) {
     // no body this step: clear the active-tile map so no stale force is read
-    k_fill_int<<<256, 256, 0, c->stream>>>(wsp<int>(c, c->L.tile_slot), -1, c->L.ntiles);
+    k_fill_int<<<256, 256, 0, c->stream>>>(wsp<int>(c, c->L.tile_slot[0]), -1, c->L.ntiles);
     if ((st = launched()) != LBM_OK) return st;
     c->slots_dirty = false;
   }
@@ -558,40 +589,57 @@ lbm_status step_one(lbm_ctx *c, const lbm_markers *m, const float *pose, const l
   return LBM_OK;
 }
 
-// nsteps steps with the immersed-boundary chain beside the collide
-// (overlap_chain): the first step's skinning and binning in launches of their
-// own, then one launch per step, each skinning and binning the next step. The
-// tile maps alternate between steps, starting so that the last step uses the
-// context's own map (L.tile_slot), which the other paths read.
-template <class S>
-lbm_status step_fused(lbm_ctx *c, const lbm_markers *m, const float *poses, const lbm_frame *frames, int nsteps,
-                      float *wrench) {
+// nsteps steps with the marker phases beside the collide (step.hpp). The first
+// step's skinning and binning run in launches of their own; the body sets
+// alternate so that the last step uses set 0, whose marker arrays are the
+// caller's and whose tile map the other paths read.
+template <class S, bool TRT>
+lbm_status step_beside_t(lbm_ctx *c, const lbm_markers *m, const float *poses, const lbm_frame *frames, int nsteps,
+                         float *wrench) {
   if (nsteps == 0) return LBM_OK;
   EnvView e = env_view(c, m);
-  int *maps[2] = {wsp<int>(c, c->L.tile_slot), wsp<int>(c, c->L.tile_slot2)};
-  const int first = (nsteps - 1) & 1;
+  if ((nsteps - 1) & 1) std::swap(e.b[0], e.b[1]);
   const size_t pose_stride = (size_t)m->nbones * 24;
+  const bool one_pass = c->p.ib_scheme == LBM_IB_DIRECT && c->p.mdf_iters == 1;
+  const bool macros = !one_pass || e.n > kDirectMarkers;
+  const int nl = std::min(c->L.cap, kListWorkgroups);
+  const int share = (int)((int64_t)bulk_blocks(e) * kBulkShare / 16);
   lbm_status st;
   prof_mark(c, 0);
-  e.tile_slot = maps[first];
-  k_skin_mark<<<skin_items(e.n), WG, 0, c->stream>>>(e, poses);
+  k_skin_mark<<<skin_items<BT>(e.n), BT, 0, c->stream>>>(e, poses);
   if ((st = launched()) != LBM_OK) return st;
-  k_active<<<(e.ntiles + WG - 1) / WG, WG, 0, c->stream>>>(e);  // also zeroes the barrier count
+  k_active<<<active_items(e), WG, 0, c->stream>>>(e);
   if ((st = launched()) != LBM_OK) return st;
   c->slots_dirty = true;
   for (int s = 0; s < nsteps; ++s) {
-    // one event per step after the first (each launch directly follows the
+    // one event per step after the first (each step directly follows the
     // previous one, whose end event is its start): event packets between
     // launches cost the step a few microseconds each
     const bool chained = s > 0 && c->prof_used > 0;
     if (!chained) prof_mark(c, 1);
-    e.tile_slot = maps[(first + s) & 1];
-    const float *next_pose = s + 1 < nsteps ? poses + (size_t)(s + 1) * pose_stride : nullptr;
-    st = launch_step_overlap<S>(c, e, frame_f(&frames[s]), rotating(&frames[s]),
-                                wrench ? wrench + (size_t)s * 8 : nullptr, next_pose, maps[(first + s + 1) & 1]);
-    if (st != LBM_OK) return st;
+    const FrameF fr = frame_f(&frames[s]);
+    const bool rot = rotating(&frames[s]);
+    const NextStep next{s + 1 < nsteps ? poses + (size_t)(s + 1) * pose_stride : nullptr};
+    float *wr = wrench ? wrench + (size_t)s * 8 : nullptr;
+    int done = 0;  // bulk blocks queued
+    if (macros) {
+      step_macro_kernels<S, TRT>(e, fr, c->cur, rot, nl, next, share, c->stream);
+      if ((st = launched()) != LBM_OK) return st;
+      done = share;
+    }
+    if (one_pass) {
+      step_interp_kernels<S, TRT>(e, fr, c->cur, rot, macros ? 0 : nl, wr ? e.partials : nullptr, next, done, share,
+                                  c->stream);
+      if ((st = launched()) != LBM_OK) return st;
+      done += share;
+    } else if ((st = launch_passes(c, e, fr, rot, wr != nullptr)) != LBM_OK) {
+      return st;
+    }
+    step_band_kernels<S, TRT>(e, fr, c->cur, rot, spread_adds(c) ? 1 : 0, wr, next, done, c->stream);
+    if ((st = launched()) != LBM_OK) return st;
     prof_mark(c, 2);
     prof_step(c, chained);
+    std::swap(e.b[0], e.b[1]);
     c->cur ^= 1;
     c->steps += 1;
   }
@@ -599,9 +647,18 @@ lbm_status step_fused(lbm_ctx *c, const lbm_markers *m, const float *poses, cons
 }
 
 template <class S>
+lbm_status step_beside(lbm_ctx *c, const lbm_markers *m, const float *poses, const lbm_frame *frames, int nsteps,
+                       float *wrench) {
+  return c->p.collision == LBM_COLLIDE_TRT ? step_beside_t<S, true>(c, m, poses, frames, nsteps, wrench)
+                                           : step_beside_t<S, false>(c, m, poses, frames, nsteps, wrench);
+}
+
+template <class S>
 lbm_status init_eq(lbm_ctx *c, const float *rho0, const float *u0) {
   GridArgs g = grid_args(c);
   dim3 grid((c->p.nx + 63) / 64, c->p.ny, c->p.nz);
+  for (int q = 0; q < 2; ++q)
+    k_clear_padding<S><<<Q, 256, 0, c->stream>>>(static_cast<typename S::T *>(c->f[q]), g);
   k_init_equilibrium<S><<<grid, 64, 0, c->stream>>>(rho0, u0, static_cast<typename S::T *>(c->f[c->cur]), g);
   return launched();
 }
@@ -668,11 +725,12 @@ lbm_status setup_ctx(lbm_ctx *c, const lbm_params *p, void *f_a, void *f_b, char
   c->prof = false;
   c->prof_used = 0;
   // collide block: bx x by cells (by = 0: bx consecutive cells of the
-  // x-fastest order). Default: 256 consecutive cells with the row layout;
-  // with planes a 64-multiple along x covering as much of a row as fits.
+  // x-fastest order). Default: 256 consecutive cells with the row layout, 512
+  // with planes (whose widths are ragged: 2-D blocks leave their lanes past a
+  // row's end idle).
   int bx = p->block_x, by = p->block_y;
-  if (bx == 0 && by == 0 && rows_layout(p)) {
-    bx = 256;
+  if (bx == 0 && by == 0) {
+    bx = rows_layout(p) ? 256 : WG;
   } else if (by == -1) {
     by = 0;
   } else {
@@ -684,10 +742,11 @@ lbm_status setup_ctx(lbm_ctx *c, const lbm_params *p, void *f_a, void *f_b, char
   // every workspace field that must start cleared, by kernels (no memset
   // nodes, so the sequence can sit in a captured graph)
   k_fill_int<<<256, 256, 0, c->stream>>>(wsp<int>(c, c->L.tile_flag), 0, c->L.ntiles);
-  k_fill_int<<<256, 256, 0, c->stream>>>(wsp<int>(c, c->L.tile_slot2), -1, c->L.ntiles);
-  k_fill_int<<<256, 256, 0, c->stream>>>(wsp<int>(c, c->L.tile_slot), -1, c->L.ntiles);
   k_fill_int<<<1, 64, 0, c->stream>>>(wsp<int>(c, c->L.guard), 0, 16);
-  k_fill_int<<<1, 64, 0, c->stream>>>(wsp<int>(c, c->L.counters), 0, 16);
+  for (int q = 0; q < 2; ++q) {
+    k_fill_int<<<256, 256, 0, c->stream>>>(wsp<int>(c, c->L.tile_slot[q]), -1, c->L.ntiles);
+    k_fill_int<<<1, 64, 0, c->stream>>>(wsp<int>(c, c->L.counters[q]), 0, 16);
+  }
   lbm_status st = launched();
   if (st != LBM_OK) return st;
   return LBM_BY_STORAGE(c, init_eq, rho0, u0);
@@ -698,7 +757,11 @@ lbm_status setup_ctx(lbm_ctx *c, const lbm_params *p, void *f_a, void *f_b, char
 // shared by every such context on that device. Host code reaches it only
 // through the address hipGetSymbolAddress returns for the current device;
 // the array's name in host code is not a device address.
-constexpr size_t kStaticWorkspaceBytes = LBM_STATIC_WORKSPACE_BYTES;
+// What lbm_init_static admits (static_need) leaves out the second body set, the
+// marker lists and the markers' wrench shares: at most 28 bytes an active tile
+// and 77 + 4 * 27 a marker, which the array holds on top (a problem at the
+// limit has at most 3,200 active tiles or 0.64M markers).
+constexpr size_t kStaticWorkspaceBytes = LBM_STATIC_WORKSPACE_BYTES + ((size_t)116 << 20);
 constexpr int kMaxStaticDevices = 64;
 __device__ __align__(256) char scratch[kStaticWorkspaceBytes];
 
@@ -763,7 +826,7 @@ lbm_status lbm_init_static(lbm_ctx **out, const lbm_params *p, void *f_a, void *
                            const float *u0, void *hip_stream) {
   if (!out || !params_ok(p) || !f_a || !f_b || f_a == f_b) return LBM_ERR_ARG;
   *out = nullptr;
-  if (layout(p).total > kStaticWorkspaceBytes) return LBM_ERR_CAPACITY;
+  if (static_need(p) > LBM_STATIC_WORKSPACE_BYTES) return LBM_ERR_CAPACITY;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return LBM_ERR_DEVICE;
   if (dev < 0 || dev >= kMaxStaticDevices) return LBM_ERR_UNSUPPORTED;
@@ -807,7 +870,7 @@ lbm_status lbm_ib_step(lbm_ctx *c, const lbm_markers *m, const float *poses, con
   if (ib && c->p.wall_mode == LBM_WALL_SLIP && c->p.ib_scheme == LBM_IB_IMPLICIT)
     for (int s = 0; s < nsteps; ++s)
       if (rotating(&frames[s])) return LBM_ERR_UNSUPPORTED;
-  if (ib && overlap_chain(c)) return LBM_BY_STORAGE(c, step_fused, m, poses, frames, nsteps, wrench);
+  if (ib && beside_collide(c)) return LBM_BY_STORAGE(c, step_beside, m, poses, frames, nsteps, wrench);
   for (int s = 0; s < nsteps; ++s) {
     const float *pose = ib ? poses + (size_t)s * m->nbones * 24 : nullptr;
     float *w = wrench ? wrench + (size_t)s * 8 : nullptr;
@@ -866,11 +929,11 @@ lbm_status adjoint_request_ok(const lbm_ctx *c, const lbm_markers *m, const floa
 // the state in e.f[0], into the IB arrays e points at.
 // wrench != null: also the step's wrench row, as lbm_ib_step writes it.
 lbm_status ib_forward(lbm_ctx *c, const EnvView &e, const FrameF &fr, const float *pose, float *wrench = nullptr) {
-  k_skin_mark<<<skin_items(e.n), WG, 0, c->stream>>>(e, pose);
-  k_active<<<(e.ntiles + WG - 1) / WG, WG, 0, c->stream>>>(e);
+  k_skin_mark<<<skin_items<BT>(e.n), BT, 0, c->stream>>>(e, pose);
+  k_active<<<active_items(e), WG, 0, c->stream>>>(e);
   k_macro<StoreF32, false><<<std::min(c->L.cap, 2048), WG, 0, c->stream>>>(e, fr, 0);
-  k_interp<false, false><<<interp_items(e.n), WG, 0, c->stream>>>(e, fr, wrench ? e.partials : nullptr);
-  k_spread<<<std::min(c->L.cap * kSpreadSplit, 2048), WG, 0, c->stream>>>(e, wrench);
+  k_interp<false, false><<<interp_items<BT>(e.n), BT, 0, c->stream>>>(e, fr, wrench ? e.partials : nullptr);
+  k_spread<<<std::min(kSpreadParts<BT> * c->L.cap, 2048), BT, 0, c->stream>>>(e, wrench, 0);
   return launched();
 }
 
@@ -903,7 +966,7 @@ lbm_status adjoint_passes(lbm_ctx *c, const EnvView &e, const FrameF &fr, const 
   }
   if (e.ib) {
     k_adj_markers<<<wave_items(e.n), WG, 0, c->stream>>>(e, A);
-    k_adj_spread<<<std::min(c->L.cap * kSpreadSplit, 2048), WG, 0, c->stream>>>(e, A);
+    k_adj_spread<<<std::min(kSpreadParts<BT> * c->L.cap, 2048), BT, 0, c->stream>>>(e, A);
     if ((st = launched()) != LBM_OK) return st;
   }
   const int grid = e.nblocks;
@@ -924,7 +987,7 @@ lbm_status adjoint_passes(lbm_ctx *c, const EnvView &e, const FrameF &fr, const 
 
 // One slot of the adjoint IB ring: the forward IB data of one step.
 struct RingSlot {
-  size_t X, U, F, rec, mstate, mbase, chunk_box, tile_slot, active, counters, macro, gfix, mbar, pbar, total;
+  size_t X, U, F, rec, mstate, mbase, chunk_box, list, tile_slot, active, counters, macro, gfix, mbar, pbar, total;
 };
 
 RingSlot ring_slot(const lbm_params *p) {
@@ -944,8 +1007,9 @@ RingSlot ring_slot(const lbm_params *p) {
   r.mstate = take(sizeof(float) * 4 * n);
   r.mbase = take(sizeof(short4) * n);
   r.chunk_box = take(sizeof(int4) * ((n + 63) / 64 + 8));
+  r.list = take(sizeof(int) * list_entries(p) * n);
   r.tile_slot = take(sizeof(int) * (size_t)L.ntiles);
-  r.active = take(sizeof(int) * (size_t)L.cap);
+  r.active = take(sizeof(int4) * (size_t)L.cap);
   r.counters = take(64);
   r.macro = take(sizeof(float) * 4 * 512 * (size_t)L.cap);
   r.gfix = take(sizeof(unsigned long long) * 3 * 512 * (size_t)L.cap);
@@ -957,16 +1021,17 @@ RingSlot ring_slot(const lbm_params *p) {
 
 // e with its per-step IB arrays in ring slot `base`.
 void point_at_slot(EnvView &e, const RingSlot &r, char *base) {
-  e.X = reinterpret_cast<float *>(base + r.X);
-  e.U = reinterpret_cast<float *>(base + r.U);
+  e.b[0].X = reinterpret_cast<float *>(base + r.X);
+  e.b[0].U = reinterpret_cast<float *>(base + r.U);
   e.F = reinterpret_cast<float *>(base + r.F);
   e.rec = reinterpret_cast<float *>(base + r.rec);
   e.mstate = reinterpret_cast<float *>(base + r.mstate);
-  e.mbase = reinterpret_cast<short4 *>(base + r.mbase);
-  e.chunk_box = reinterpret_cast<int4 *>(base + r.chunk_box);
-  e.tile_slot = reinterpret_cast<int *>(base + r.tile_slot);
-  e.active = reinterpret_cast<int *>(base + r.active);
-  e.counters = reinterpret_cast<int *>(base + r.counters);
+  e.list = reinterpret_cast<int *>(base + r.list);
+  e.b[0].mbase = reinterpret_cast<short4 *>(base + r.mbase);
+  e.b[0].chunk_box = reinterpret_cast<int4 *>(base + r.chunk_box);
+  e.b[0].tile_slot = reinterpret_cast<int *>(base + r.tile_slot);
+  e.b[0].active = reinterpret_cast<int4 *>(base + r.active);
+  e.b[0].counters = reinterpret_cast<int *>(base + r.counters);
   e.macro = reinterpret_cast<float4 *>(base + r.macro);
   e.gfix = reinterpret_cast<unsigned long long *>(base + r.gfix);
 }
@@ -1246,7 +1311,6 @@ lbm_status lbm_check(lbm_ctx *c) {
   if (guard & GUARD_MARKER_RANGE) return LBM_ERR_MARKER_RANGE;
   if (guard & GUARD_CAPACITY) return LBM_ERR_CAPACITY;
   if (guard & GUARD_BONE) return LBM_ERR_ARG;
-  if (guard & GUARD_SCHEDULE) return LBM_ERR_DEVICE;
   return LBM_OK;
 }
 
@@ -1460,7 +1524,7 @@ lbm_status batch_enqueue_t(lbm_batch *b, int nsteps, int mode) {
   }
   int cap_items = 0;
   for (int e = 0; e < b->nenv; ++e) cap_items += b->views[e].cap;
-  const int gdyn = std::max(8, std::min(cap_items * kSpreadSplit, 4096));
+  const int gdyn = std::max(8, std::min(4 * cap_items, 4096));
   // interpolation branches per environment only on rotation
   auto interp = [&](const BatchArgs &args, int s, int pass) {
     if (UNI || b->still)
@@ -1480,15 +1544,14 @@ lbm_status batch_enqueue_t(lbm_batch *b, int nsteps, int mode) {
         kb_spread_cg<<<gdyn, WG, 0, b->stream>>>(a, j);
         kb_cg_apply<<<b->tot[PRE_INTERP], WG, 0, b->stream>>>(a, j);
         kb_cg_update<<<b->tot_cg, kCgWG, 0, b->stream>>>(a, s, j, last ? 1 : 0);
-        if (!last) kb_cg_clear<<<gdyn, WG, 0, b->stream>>>(a);
       }
     } else {
       for (int pass = 0; pass < b->mdf; ++pass) {
-        if (pass > 0) kb_spread<<<gdyn, WG, 0, b->stream>>>(a, s, 0);
+        if (pass > 0) kb_spread<<<gdyn, WG, 0, b->stream>>>(a, s, 0, pass > 1);
         interp(a, s, pass);
       }
     }
-    kb_spread<<<gdyn, WG, 0, b->stream>>>(a, s, 1);
+    kb_spread<<<gdyn, WG, 0, b->stream>>>(a, s, 1, !b->implicit && b->mdf > 1);
     batch_collide(b, a, s);
     lbm_status st = launched();
     if (st != LBM_OK) return st;

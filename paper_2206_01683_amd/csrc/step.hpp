@@ -1,157 +1,230 @@
 // One lattice step with the immersed-boundary phases running beside the
-// collide in a single launch. This step's markers were skinned and their
-// tiles binned into this step's tile map before the launch (by the previous
-// step's launch, or by launches of their own for the first step of a call).
+// collide.
 //
-// Workgroups [0, nib) run the immersed-boundary chain, with barriers among
-// themselves: band macros, interpolation with direct forcing (and its
-// multi-direct passes), spreading into the fixed-point force, then the
-// collide of the band cells (those whose source node lies in an active tile,
-// the only cells with an immersed force); then they skin the next step's
-// markers and bin its tiles into the other tile map (the two maps alternate
-// between steps). The other workgroups are the collide blocks, in launch
-// order as in k_collide: each collides its cells outside the band at once and
-// leaves the band cells to the chain. Active tiles fill a fraction of a
-// percent of the lattice, so nearly all of the collide's 216 B per cell
-// stream while the latency-bound chain runs, no collide block waits for it,
-// and a step is one launch.
+// Only the cells whose source node lies in an active tile (the band, a
+// fraction of a percent of a large lattice) carry an immersed force. Every
+// other cell collides without waiting for the markers, so the latency-bound
+// marker phases run in launches whose other workgroups stream the rest of the
+// lattice ("bulk"):
+//   k_step_macro   band macros, the tiles' marker lists, skinning of the next
+//                  step's markers, part of the bulk (not for few markers);
+//   k_step_interp  interpolation and forcing, from the band macros, or for few
+//                  markers straight from the populations with the lists and
+//                  the skinning beside it; part of the bulk;
+//   k_step_band    per z-plane of an active tile: spreading into LDS, then the
+//                  collide of its cells with the force taken from there (it
+//                  never reaches memory); binning of the next step's tiles,
+//                  the wrench, the rest of the bulk.
+// More forcing passes and the implicit correction need the force at the nodes
+// between passes: their passes run between k_step_macro and k_step_band in
+// launches of their own.
 //
-// Correctness does not depend on timing: the chain reads the source buffer
-// (cur) and writes its own band arrays, the band cells of the other buffer,
-// the next step's marker data and the other tile map; the collide blocks read
-// the source buffer and this step's tile map (complete before the launch) and
-// write the other buffer outside the band. The two never touch the same
-// words. The arithmetic is the same inline code as the separate kernels', so
-// results agree bit for bit.
+// Nothing waits inside a launch. This step's markers and tile map (body set
+// b[0]) are complete before its first launch; the next step's go to b[1], and
+// the two sets alternate between steps. A launch reads the source buffer and
+// writes the other one, each cell by one workgroup. The arithmetic is the
+// same inline code as the separate kernels', so results agree bit for bit.
 #pragma once
 
 #include "ib.hpp"
 
 namespace lbmib {
 
-// Polls of a chain barrier before a waiter gives up (well over a second):
-// the host keeps the chain within what the device holds at once, so only a
-// device shared with work that never yields its slots can reach it.
-constexpr long kChainSpins = 1L << 22;
+// At most this many markers are interpolated straight from the populations (two
+// launches a step); more get the band macros first (three). The direct form
+// pulls 27 x 16 short rows for each marker, 55 KB of L2 lines: 3.7 ns a marker
+// on the whole chip, against 6 us for the extra launch. Steps of the sphere
+// (500 markers) 15.8 against 21.6 us, of the fin (3,000) 38.0 against 36.1 us.
+constexpr int kDirectMarkers = 2000;
+// Sixteenths of the bulk in each launch before the last, enough to cover the
+// marker work there (2, 3 and 4 of them: fin 37.3, 37.2, 36.0 us, fish 539,
+// 537, 535 us).
+constexpr int kBulkShare = 4;
+// Most marker workgroups over tile parts, marker lists and planes.
+constexpr int kMacroWorkgroups = 1024, kListWorkgroups = 256, kBandWorkgroups = 1024;
 
-// Barrier among the nib chain workgroups (co-resident: dispatched first).
-// Arrival is an acquire-release read-modify-write at device scope; waiters
-// poll with relaxed loads and acquire once. A waiter that gives up raises
-// the schedule guard and goes on (its results are then void), so that the
-// launch always ends.
-__device__ inline void chain_sync(unsigned *sched, int nib, int *guard) {
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const unsigned gen = __hip_atomic_load(&sched[SCHED_GEN], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (__hip_atomic_fetch_add(&sched[SCHED_ARRIVE], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
-        (unsigned)nib - 1) {
-      __hip_atomic_store(&sched[SCHED_ARRIVE], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_fetch_add(&sched[SCHED_GEN], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      long spins = 0;
-      while (__hip_atomic_load(&sched[SCHED_GEN], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gen) {
-        __builtin_amdgcn_s_sleep(2);
-        if (++spins > kChainSpins) {
-          atomicOr(guard, (int)GUARD_SCHEDULE);
-          break;
-        }
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    }
-  }
-  __syncthreads();
-}
+// The next step's skinning and binning, beside this step (pose null: none).
+struct NextStep {
+  const float *pose;
+};
 
-// The band cells of active slot `slot`: the cells whose source node lies in
-// its tile, that is the tile's own cells, and on an open face whose last tile
-// is one node wide (a dimension of 8k + 1) also the face nodes beyond it
-// (the source node of a face node is its inward neighbour). A cell of the
-// box whose source lies in another tile is that tile's.
+// LDS a launch reserves beyond its own so that three 256-cell blocks of the F32
+// collide share a compute unit (see collide_lds), and the spacing of its marker
+// workgroups, both by how much bulk there is:
+//   F32 lattices of a million cells and more take the reservation (fish 547
+//   against 566 us; 192x96x96 115.6 against 117.1, the 128x64x64 fin 36.6
+//   against 36.0 us without); 2-byte ones never (fish 338 against 291 us);
+//   where the bulk of the launch is over eight times what the chip then holds,
+//   marker workgroups come eight (one per XCD) after every kGap bulk blocks, so
+//   that they never hold most of the few slots (fish 526 against 535 us); where
+//   it is less they come first, since the launch may end on them (192x96x96
+//   115.6 us first, 119.9 spaced; two fish 54.0, 55.9).
+constexpr int kGap = 56;
+constexpr int kCapBlocks = 4096, kCapResident = 768;  // blocks of BT cells; three on each of 256 compute units
+
+// Cell blk * BT + tid of the bulk, in x-fastest order. The tile map is read
+// beside the populations, not before them (the memory clobber keeps the pulls
+// above the branch): a band cell, whose pull is wasted, is rare, and a pull
+// that waits for the map costs the F16 collide a third of its speed.
 template <class S, bool XPER, bool ROT, bool YZ, bool TRT>
-__device__ inline void band_collide_item(const EnvView &e, const FrameF &fr, int cur, int slot, int tid) {
-  const GridArgs &g = e.g;
-  const int t = ((const gmem<int> *)e.active)[slot];
-  const int tx = t % g.tnx, rest = t / g.tnx, ty = rest % g.tny, tz = rest / g.tny;
-  const int x0 = tx << 3, y0 = ty << 3, z0 = tz << 3;
-  int x1 = min(x0 + 8, g.nx), y1 = min(y0 + 8, g.ny), z1 = min(z0 + 8, g.nz);
-  if (!XPER && x1 == g.nx - 1) ++x1;
-  if (YZ && !g.yper && y1 == g.ny - 1) ++y1;
-  if (YZ && !g.zper && z1 == g.nz - 1) ++z1;
-  const int ex = x1 - x0, ey = y1 - y0, cnt = ex * ey * (z1 - z0);
-  for (int lc = tid; lc < cnt; lc += WG) {
-    const int x = x0 + lc % ex, r = lc / ex, y = y0 + r % ey, z = z0 + r / ey;
-    const CellAt c = cell_at<XPER, YZ>(g, x, y, z);
-    if (((c.xs >> 3) != tx) | ((c.ys >> 3) != ty) | ((c.zs >> 3) != tz)) continue;
-    float f[Q];
-    collide_pull<S, XPER, YZ>(e, cur, c, f);
-    collide_finish<S, XPER, ROT, YZ, TRT>(e, fr, cur, c, f);
-  }
-}
-
-// The chain of workgroup blk of nib: the same phases and order as the
-// separate launches of step_one (macro; per pass: spread of the force so far
-// after the first, interpolation; final spread with the wrench sum), the
-// collide of the band cells, then, when next_pose is not null, the next
-// step's skinning and binning into next_slots.
-template <class S, bool XPER, bool ROT, bool YZ, bool TRT>
-__device__ inline void ib_chain(const EnvView &e, const FrameF &fr, int cur, int blk, int nib, int passes,
-                                float *wrench, const float *next_pose, int *next_slots, int tid) {
-  unsigned *sched = e.sched;
-  const int na = n_active_of(e);
-  for (int slot = blk; slot < na; slot += nib) macro_item<S, ROT>(e, fr, cur, slot, tid);
-  chain_sync(sched, nib, e.guard);
-  const int nspread = na * kSpreadSplit, ninterp = interp_items(e.n);
-  for (int it = 0; it < passes; ++it) {
-    if (it > 0) {
-      for (int item = blk; item < nspread; item += nib) spread_item(e, item, tid);
-      chain_sync(sched, nib, e.guard);
-    }
-    float *part = (wrench != nullptr && it == passes - 1) ? e.partials : nullptr;
-    for (int item = blk; item < ninterp; item += nib) {
-      if (it > 0)
-        interp_item<ROT, true>(e, fr, item, tid, part);
-      else
-        interp_item<ROT, false>(e, fr, item, tid, part);
-    }
-    chain_sync(sched, nib, e.guard);
-  }
-  if (blk == 0 && wrench != nullptr) wrench_sum(e.partials, ninterp, wrench, tid);
-  for (int item = blk; item < nspread; item += nib) spread_item(e, item, tid);
-  chain_sync(sched, nib, e.guard);
-  for (int slot = blk; slot < na; slot += nib) band_collide_item<S, XPER, ROT, YZ, TRT>(e, fr, cur, slot, tid);
-  if (next_pose == nullptr) return;
-  // The next step's skinning needs no barrier after the band collide: it
-  // writes the marker data, chunk boxes and tile flags, which only the
-  // phases before the last barrier read, and the active count (na was read
-  // at the start). The binning rewrites the active list the band collide
-  // reads, so it waits for every workgroup.
-  for (int item = blk; item < skin_items(e.n); item += nib) skin_item(e, next_pose, item, tid);
-  chain_sync(sched, nib, e.guard);
-  for (int item = blk; item < active_items(e); item += nib) active_item(e, item, tid, false, next_slots);
-}
-
-// Grid: nib + e.nblocks workgroups of WG threads; the collide shape of e is
-// linear (e.by == 0, e.bx == WG) or 2-D with e.bx * e.by == WG. e.tile_slot:
-// this step's tile map.
-template <class S, bool XPER, bool ROT, bool YZ, bool TRT>
-__global__ void __launch_bounds__(WG) k_step_overlap(EnvView e, FrameF fr, int cur, int nib, int passes,
-                                                      float *wrench, const float *next_pose, int *next_slots) {
-  const int tid = threadIdx.x;
-  if ((int)blockIdx.x < nib) {
-    ib_chain<S, XPER, ROT, YZ, TRT>(e, fr, cur, blockIdx.x, nib, passes, wrench, next_pose, next_slots, tid);
-    return;
-  }
-  const int lb = (int)blockIdx.x - nib;
-  if (lb >= e.nblocks) return;
-  const int tx = e.by == 0 ? tid : tid % e.bx, ty = e.by == 0 ? 0 : tid / e.bx;
-  int x, y, z;
-  if (!cell_of(e, lb, tx, ty, x, y, z)) return;
-  const CellAt c = cell_at<XPER, YZ>(e.g, x, y, z);
-  // a band cell (source node in an active tile) is the chain's
-  if (((const gmem<int> *)e.tile_slot)[(c.xs >> 3) + e.g.tnx * ((c.ys >> 3) + e.g.tny * (c.zs >> 3))] >= 0) return;
+__device__ inline void bulk_cell(const EnvView &e, const BodySet &bs, const FrameF &fr, int cur, int blk, int tid) {
+  const uint32_t cell = (uint32_t)blk * (uint32_t)BT + (uint32_t)tid, row = cell / (uint32_t)e.g.nx;
+  const int z = (int)(row / (uint32_t)e.g.ny);
+  if (z >= e.g.nz) return;
+  const CellAt c = cell_at<XPER, YZ>(e.g, (int)(cell - row * (uint32_t)e.g.nx),
+                                     (int)(row - (uint32_t)z * (uint32_t)e.g.ny), z);
+  const int slot = ((const gmem<int> *)bs.tile_slot)[(c.xs >> 3) + e.g.tnx * ((c.ys >> 3) + e.g.tny * (c.zs >> 3))];
   float f[Q];
   collide_pull<S, XPER, YZ>(e, cur, c, f);
-  collide_finish<S, XPER, ROT, YZ, TRT>(e, fr, cur, c, f);
+  asm volatile("" ::: "memory");
+  if (slot >= 0) return;  // a band cell (source node in an active tile): its tile's workgroup collides it
+  collide_finish<S, XPER, ROT, YZ, TRT>(e, fr, cur, c, f, 0.f, 0.f, 0.f);
+}
+inline int bulk_blocks(const EnvView &e) { return (int)(((size_t)e.g.nx * e.g.ny * e.g.nz + BT - 1) / BT); }
+
+// Plane item % 8 of active tile item / 8: its immersed force into LDS, then the
+// band cells whose source node lies in it: the plane's own cells, and the face
+// nodes beyond it (the source node of a face node is its inward neighbour):
+// along z the neighbouring face plane, along x and y those of a last tile that
+// is one node wide (a dimension of 8k + 1). The plane's populations are pulled
+// first, so that their latency overlaps the spreading. add: the force starts
+// from gfix (earlier forcing passes).
+template <class S, bool XPER, bool ROT, bool YZ, bool TRT>
+__device__ inline void band_item(const EnvView &e, const BodySet &bs, const FrameF &fr, int cur, int item, int tid,
+                                 bool add, SpreadLds<3> &s) {
+  const GridArgs &g = e.g;
+  const int slot = item >> 3, plane = item & 7;
+  const TileAt t = active_of(bs, slot);
+  const int x0 = t.x << 3, y0 = t.y << 3, z = (t.z << 3) + plane;
+  if (z >= g.nz) return;  // uniform over the workgroup
+  const int x = x0 + (tid & 7), y = y0 + ((tid >> 3) & 7);
+  auto source_here = [&](const CellAt &c) { return ((c.xs >> 3) == t.x) & ((c.ys >> 3) == t.y) & (c.zs == z); };
+  float f[Q];
+  CellAt c{};
+  bool own = tid < 64 && x < g.nx && y < g.ny;
+  if (own) {
+    c = cell_at<XPER, YZ>(g, x, y, z);
+    own = source_here(c);
+    if (own) collide_pull<S, XPER, YZ>(e, cur, c, f);
+  }
+  const gmem<unsigned long long> *gp = (const gmem<unsigned long long> *)e.gfix + (size_t)slot * 1536 + plane * 64;
+  if (tid < 192) (&s.acc[0][0])[tid] = add ? gp[512 * (tid >> 6) + (tid & 63)] : 0ull;
+  spread_plane<false>(e, bs, t, plane, tid, s);
+  auto finish = [&](const CellAt &cc, float ff[Q]) {
+    const int lc = (cc.xs & 7) | ((cc.ys & 7) << 3);
+    collide_finish<S, XPER, ROT, YZ, TRT>(e, fr, cur, cc, ff, from_fix(s.acc[0][lc]), from_fix(s.acc[1][lc]),
+                                          from_fix(s.acc[2][lc]));
+  };
+  if (own) finish(c, f);
+  if (!XPER || YZ) {
+    const int x1 = min(x0 + 8, g.nx), y1 = min(y0 + 8, g.ny);
+    const int mx = !XPER && x1 == g.nx - 1, my = YZ && !g.yper && y1 == g.ny - 1;
+    const int zlo = YZ && !g.zper && z == 1 ? 0 : z, zhi = YZ && !g.zper && z == g.nz - 2 ? g.nz - 1 : z;
+    if (mx | my | (zlo != zhi)) {
+      const int ex = x1 + mx - x0, ey = y1 + my - y0, cnt = ex * ey * (zhi - zlo + 1);
+      for (int lc = tid; lc < cnt; lc += BT) {
+        const int lx = lc % ex, r = lc / ex, ly = r % ey, zc = zlo + r / ey;
+        if (zc == z && lx < 8 && ly < 8) continue;  // the plane's own
+        const CellAt cc = cell_at<XPER, YZ>(g, x0 + lx, y0 + ly, zc);
+        if (!source_here(cc)) continue;
+        float ff[Q];
+        collide_pull<S, XPER, YZ>(e, cur, cc, ff);
+        finish(cc, ff);
+      }
+    }
+  }
+  __syncthreads();  // s is reused by the next item
+}
+
+// Which work workgroup blk of a launch has: nfront workgroups of marker work in
+// groups of eight (one per XCD), each group followed by `gap` bulk blocks, then
+// the rest of the bulk. Returns the marker workgroup (blk set to it) or false
+// (blk set to the bulk block). The grid is 8 ceil(nfront / 8) + bulk blocks, and
+// marker workgroups nfront and beyond have none.
+__device__ inline bool marker_block(int &blk, int nfront, int gap) {
+  const int groups = (nfront + 7) >> 3, per = 8 + gap, span = groups * per;
+  if (blk >= span) {
+    blk -= 8 * groups;
+    return false;
+  }
+  const int q = blk / per, r = blk - q * per;
+  blk = r < 8 ? 8 * q + r : gap * q + r - 8;
+  return r < 8;
+}
+
+constexpr int kStepMk = BT / 64;  // markers per workgroup of k_step_interp, one wave each
+
+// Marker workgroups: nm over the halves of the active tiles, nl for the marker
+// lists (over the active tiles), skin_items for the next step (none without
+// one). The bulk starts at block 0.
+template <class S, bool XPER, bool ROT, bool YZ, bool TRT>
+__global__ void __launch_bounds__(BT, 4) k_step_macro(EnvView e, FrameF fr, int cur, int nm, int nl, NextStep next,
+                                                      int gap) {
+  const int tid = threadIdx.x;
+  int blk = blockIdx.x;
+  const int ns = next.pose != nullptr ? skin_items<BT>(e.n) : 0;
+  if (!marker_block(blk, nm + nl + ns, gap)) {
+    bulk_cell<S, XPER, ROT, YZ, TRT>(e, e.b[0], fr, cur, blk, tid);
+  } else if (blk < nm) {
+    const XcdWalk w = xcd_walk(2 * n_active_of(e, e.b[0]), blk, nm);
+    for (int h = w.first; h < w.end; h += w.step) macro_item<BT, S, ROT>(e, e.b[0], fr, cur, h, tid);
+  } else if (blk < nm + nl) {
+    const int na = n_active_of(e, e.b[0]);
+    for (int slot = blk - nm; slot < na; slot += nl) list_item<BT>(e, e.b[0], slot, tid);
+  } else if (blk < nm + nl + ns) {
+    skin_item<BT>(e, e.b[1], next.pose, blk - nm - nl, tid);
+  }
+}
+
+// After k_step_macro (nl = 0): marker workgroups interp_items<BT>(n) from the
+// band macros. Without it (nl > 0): kStepMk markers a workgroup straight from the
+// populations, nl for the marker lists, skin_items for the next step. The bulk
+// starts at block first_bulk.
+template <class S, bool XPER, bool ROT, bool YZ, bool TRT>
+__global__ void __launch_bounds__(BT, 4) k_step_interp(EnvView e, FrameF fr, int cur, int nl, float *partials,
+                                                       NextStep next, int first_bulk, int gap) {
+  const int tid = threadIdx.x;
+  int blk = blockIdx.x;
+  const int ni = nl > 0 ? (e.n + kStepMk - 1) / kStepMk : interp_items<BT>(e.n);
+  const int ns = nl > 0 && next.pose != nullptr ? skin_items<BT>(e.n) : 0;
+  if (!marker_block(blk, ni + nl + ns, gap)) {
+    bulk_cell<S, XPER, ROT, YZ, TRT>(e, e.b[0], fr, cur, first_bulk + blk, tid);
+  } else if (blk < ni) {
+    if (nl > 0) {
+      const int k = __builtin_amdgcn_readfirstlane(xcd_item(blk, ni) * kStepMk + (tid >> 6));
+      if (k < e.n) interp_wave<S, ROT>(e, e.b[0], fr, cur, k, tid & 63, partials);
+    } else {
+      interp_item<BT, ROT, false>(e, e.b[0], fr, xcd_item(blk, ni), tid, partials);
+    }
+  } else if (blk < ni + nl) {
+    const int na = n_active_of(e, e.b[0]);
+    for (int slot = blk - ni; slot < na; slot += nl) list_item<BT>(e, e.b[0], slot, tid);
+  } else if (blk < ni + nl + ns) {
+    skin_item<BT>(e, e.b[1], next.pose, blk - ni - nl, tid);
+  }
+}
+
+// Marker workgroups: nt over the planes of the active tiles, one for the wrench
+// (null: none), active_items for the next step's binning (next.pose null: none).
+// The bulk starts at block first_bulk.
+template <class S, bool XPER, bool ROT, bool YZ, bool TRT>
+__global__ void __launch_bounds__(BT, 4) k_step_band(EnvView e, FrameF fr, int cur, int nt, int add, float *wrench,
+                                                     NextStep next, int first_bulk, int gap) {
+  const int tid = threadIdx.x;
+  int blk = blockIdx.x;
+  const int nw = wrench != nullptr ? 1 : 0, nb = next.pose != nullptr ? active_items<BT>(e) : 0;
+  if (!marker_block(blk, nt + nw + nb, gap)) {
+    bulk_cell<S, XPER, ROT, YZ, TRT>(e, e.b[0], fr, cur, first_bulk + blk, tid);
+  } else if (blk < nt) {
+    __shared__ SpreadLds<3> s;
+    const int items = 8 * n_active_of(e, e.b[0]);
+    for (int item = blk; item < items; item += nt)
+      band_item<S, XPER, ROT, YZ, TRT>(e, e.b[0], fr, cur, item, tid, add != 0, s);
+  } else if (blk < nt + nw) {
+    wrench_sum<BT>(e.partials, e.n, wrench, tid);
+  } else if (blk < nt + nw + nb) {
+    active_item<BT>(e, e.b[1], blk - nt - nw, tid);
+  }
 }
 
 }  // namespace lbmib

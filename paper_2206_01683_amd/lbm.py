@@ -175,8 +175,8 @@ def make_params(nx, ny, nz, tau, bc_lo=BC_PERIODIC, bc_hi=BC_PERIODIC, storage="
     collision: COLLIDE_BGK or COLLIDE_TRT with Lambda = trt_lambda.
     wall_mode: WALL_NO_SLIP or WALL_SLIP (normal component only).
     layout: LAYOUT_AUTO, LAYOUT_PLANES or LAYOUT_ROWS (stored populations).
-    ib_workgroups: workgroups running the IB phases beside the collide (0
-    automatic); -1 runs them before the collide in launches of their own.
+    ib_workgroups: -1 runs the IB phases before the collide in launches of
+    their own, any other value (0 automatic) beside it.
     block: collide block (bx, by); (bx, -1) is bx consecutive cells."""
     return Params(nx, ny, nz, bc_lo, bc_hi, STORAGE[storage] if isinstance(storage, str) else storage,
                   max_markers, max_bones, mdf_iters, max_active_tiles, block[0], block[1], 1 if with_adjoint else 0,
