@@ -7,15 +7,25 @@
 // prefixes; the active-tile counts are only known on the device, so the
 // macro and spreading phases build their prefix in LDS from the counters.
 // Two drivers use the same phase functions:
-//   kb_* kernels     one launch per phase (a step = 6+ launches; the collide
-//                    one launch per collide kind present, each specialised),
-//                    suitable for capture into a graph of many steps; they
-//                    also take 2-byte storage and the implicit correction;
+//   kb_* kernels     a launch per phase: band macros and lists, interpolation with
+//                    the next step's skinning, spreading with its binning, the
+//                    collide (one launch per collide kind present, each
+//                    specialised); suitable for capture into a graph of many
+//                    steps; they also take 2-byte storage and the implicit
+//                    correction;
 //   kb_persistent    one launch for all steps: each workgroup loops over the
 //                    phases, separated by a device-wide barrier. The grid is
 //                    sized to be co-resident; the barrier's wait is bounded
 //                    (a timeout sets a status bit and every workgroup exits).
 //                    F32 storage and direct forcing only.
+// The marker phases don't run beside the collides as a lone lattice's do
+// (step.hpp): over many lattices they fill the chip, and the band, 9 % of the
+// cells of lattices this small, is read and written in 32-byte rows whose lines
+// a collide beside them drives out of L2 (48 lattices of 0.3 to 1.3 million
+// cells: macros 93 and band collides 282 us alone, 194 and 585 us more beside).
+// One step there takes 1,517 us: collide 1,316, band macros and lists 73,
+// spreading and binning 73, interpolation and skinning 55 (16 bf16 ones, two
+// groups: 143, 25, 31, 16).
 // UNI = true: every environment is of collide kind 0 (open x faces, no
 // rotation, periodic y and z, BGK, F32), so the per-environment branches on
 // those flags compile away. The interpolation branches on rotation only, so
@@ -35,7 +45,17 @@ struct BatchArgs {
   const int *corder;    // [nenv] environment at each position of the collide prefix (grouped by kind)
   int tot[4];
   int mdf;              // direct-forcing passes
+  int set;              // body set of this step (BodySet; the next step's is set ^ 1)
   unsigned *bar;        // grid barrier words and the collide work queue (BAR_*, kBarWords)
+
+  // Environment i. Nothing writes the descriptors while a kernel runs, which the
+  // constant address space says: its fields are scalar loads that may be kept
+  // over stores. Read through a plain pointer, every field was a vector load
+  // again after each store or LDS atomic, in the middle of the phases' chains.
+  __device__ const EnvView &env(int i) const {
+    using View = const __attribute__((address_space(4))) EnvView;
+    return *(const EnvView *)((View *)(uintptr_t)envs + i);
+  }
 };
 
 // Barrier words, each on its own 128-byte line (indices into BatchArgs::bar):
@@ -57,50 +77,44 @@ constexpr int kBarWords = BAR_GROUPS + kBarMaxGroups * kBarLine;
 // the collide order, corder); PRE_CG counts conjugate-gradient items.
 enum { PRE_SKIN = 0, PRE_ACTIVE = 1, PRE_INTERP = 2, PRE_COLLIDE = 3, PRE_CG = 5, PRE_ROWS = 6 };
 
-// Largest e with pre[e] <= item (pre non-decreasing, pre[nenv] > item).
+// Largest e with pre[e] <= item (pre non-decreasing, pre[nenv] > item). Called by
+// whole waves with the same item: 64 entries are compared at once, one load
+// instead of the chain of a binary search, and the environment is a scalar.
 __device__ inline int find_env(const int *pre, int nenv, int item) {
-  int lo = 0, hi = nenv;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (pre[mid] <= item)
-      lo = mid;
-    else
-      hi = mid;
+  const int lane = threadIdx.x & 63;
+  int n = 0;
+  for (int base = 0; base < nenv; base += 64) {
+    const bool le = base + lane < nenv && pre[base + lane] <= item;
+    const int cnt = __popcll(__ballot(le));
+    n += cnt;
+    if (cnt < 64) break;
   }
-  return lo;
+  return __builtin_amdgcn_readfirstlane(n - 1);
 }
+__device__ inline int uniform_i(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// Exclusive prefix over environments of (active tiles x mult), in LDS.
-// Returns the total. Every thread of the workgroup must call it. Up to 64
-// environments the first wave scans them with lane shuffles (one barrier);
-// more take the workgroup-wide scan.
+// Exclusive prefix over environments of (active tiles x mult), in LDS, scanned
+// by the first wave with lane shuffles, 64 environments at a time. Returns the
+// total. Every thread of the workgroup must call it.
 __device__ inline int dynamic_prefix(const BatchArgs &b, int mult, int *s_pre, int tid) {
-  int v = 0;
-  if (tid < b.nenv) v = n_active_of(b.envs[tid], b.envs[tid].b[0]) * mult;
-  if (b.nenv <= 64) {
-    if (tid < 64) {
-      const int lane = tid;
+  if (tid < 64) {
+    int carry = 0;
+    for (int base = 0; base < b.nenv; base += 64) {
+      int v = 0;
+      if (base + tid < b.nenv) v = n_active_of(b.env(base + tid), b.env(base + tid).b[b.set]) * mult;
 #pragma unroll
       for (int off = 1; off < 64; off <<= 1) {
-        const int up = __builtin_amdgcn_ds_bpermute((lane >= off ? lane - off : lane) << 2, v);
-        if (lane >= off) v += up;
+        const int up = __builtin_amdgcn_ds_bpermute((tid >= off ? tid - off : tid) << 2, v);
+        if (tid >= off) v += up;
       }
-      s_pre[tid + 1] = v;
-      if (tid == 0) s_pre[0] = 0;
+      v += carry;
+      if (base + tid < b.nenv) s_pre[base + tid + 1] = v;
+      carry = __builtin_amdgcn_readlane(v, 63);
     }
-    __syncthreads();
-    return s_pre[b.nenv];
+    if (tid == 0) s_pre[0] = 0;
   }
-  s_pre[tid + 1] = v;
-  if (tid == 0) s_pre[0] = 0;
   __syncthreads();
-  for (int off = 1; off < WG; off <<= 1) {
-    const int add = tid >= off ? s_pre[tid + 1 - off] : 0;
-    __syncthreads();
-    s_pre[tid + 1] += add;
-    __syncthreads();
-  }
-  return s_pre[b.nenv];
+  return uniform_i(s_pre[b.nenv]);
 }
 
 // Step s's frame of environment e. The values are uniform over the
@@ -167,32 +181,33 @@ template <> struct StoreOf<2> { using type = StoreBF16; };
 // K >= 0: the environment is of kind K (one specialised collide, registers
 // of that variant only); K < 0: any F32 kind, chosen at run time.
 template <int K>
-__device__ inline void collide_item(const EnvView &e, const FrameF &fr, int cur, int lb, int tx, int ty) {
+__device__ inline void collide_item(const EnvView &e, int set, const FrameF &fr, int cur, int lb, int tx, int ty) {
   if constexpr (K < 0)
     collide_any(e, fr, cur, lb, tx, ty);
   else
     collide_cell<typename StoreOf<(K >> 4)>::type, (K & 1) != 0, (K & 2) != 0, (K & 4) != 0, (K & 8) != 0>(
-        e, e.b[0].tile_slot, fr, cur, lb, tx, ty);
+        e, e.b[set].tile_slot, fr, cur, lb, tx, ty);
 }
 
 // ------------------------------------------------------------ phase bodies --
-__device__ inline void phase_skin(const BatchArgs &b, int s, int item, int tid) {
+// The skinning and binning of step s into body set `set`.
+__device__ inline void phase_skin(const BatchArgs &b, int s, int set, int item, int tid) {
   const int ei = find_env(b.pre + PRE_SKIN * (b.nenv + 1), b.nenv, item);
-  const EnvView &e = b.envs[ei];
-  skin_item(e, e.b[0], e.poses + (size_t)s * e.nbones * 24, item - b.pre[PRE_SKIN * (b.nenv + 1) + ei], tid);
+  const EnvView &e = b.env(ei);
+  skin_item(e, e.b[set], e.poses + (size_t)s * e.nbones * 24, item - b.pre[PRE_SKIN * (b.nenv + 1) + ei], tid);
 }
 
-__device__ inline void phase_active(const BatchArgs &b, int item, int tid) {
+__device__ inline void phase_active(const BatchArgs &b, int set, int item, int tid) {
   const int ei = find_env(b.pre + PRE_ACTIVE * (b.nenv + 1), b.nenv, item);
-  active_item(b.envs[ei], b.envs[ei].b[0], item - b.pre[PRE_ACTIVE * (b.nenv + 1) + ei], tid);
+  active_item(b.env(ei), b.env(ei).b[set], item - b.pre[PRE_ACTIVE * (b.nenv + 1) + ei], tid);
 }
 
 template <class S, bool UNI>
-__device__ inline void macro_rot(const EnvView &e, const FrameF &fr, int cur, int slot, int tid) {
+__device__ inline void macro_rot(const EnvView &e, const BodySet &bs, const FrameF &fr, int cur, int slot, int tid) {
   if (!UNI && e.rot)
-    macro_item<WG, S, true>(e, e.b[0], fr, cur, slot, tid);
+    macro_item<WG, S, true>(e, bs, fr, cur, slot, tid);
   else
-    macro_item<WG, S, false>(e, e.b[0], fr, cur, slot, tid);
+    macro_item<WG, S, false>(e, bs, fr, cur, slot, tid);
 }
 
 // ANYS: environments may store 2-byte populations (per-phase driver); the
@@ -200,48 +215,49 @@ __device__ inline void macro_rot(const EnvView &e, const FrameF &fr, int cur, in
 template <bool UNI, bool ANYS = false>
 __device__ inline void phase_macro(const BatchArgs &b, int s, int item, const int *s_pre, int tid) {
   const int ei = find_env(s_pre, b.nenv, item);
-  const EnvView &e = b.envs[ei];
+  const EnvView &e = b.env(ei);
   const FrameF fr = env_frame(e, s);
-  const int cur = env_cur(e, s), slot = item - s_pre[ei];
-  list_item<WG>(e, e.b[0], slot, tid);
+  const int cur = env_cur(e, s), slot = uniform_i(item - s_pre[ei]);
+  list_item<WG>(e, e.b[b.set], slot, tid);
   if (!UNI && ANYS && e.storage == StoreF16::kind)
-    macro_rot<StoreF16, UNI>(e, fr, cur, slot, tid);
+    macro_rot<StoreF16, UNI>(e, e.b[b.set], fr, cur, slot, tid);
   else if (!UNI && ANYS && e.storage == StoreBF16::kind)
-    macro_rot<StoreBF16, UNI>(e, fr, cur, slot, tid);
+    macro_rot<StoreBF16, UNI>(e, e.b[b.set], fr, cur, slot, tid);
   else
-    macro_rot<StoreF32, UNI>(e, fr, cur, slot, tid);
+    macro_rot<StoreF32, UNI>(e, e.b[b.set], fr, cur, slot, tid);
 }
 
 template <bool UNI>
 __device__ inline void phase_interp(const BatchArgs &b, int s, int pass, int item, int tid) {
   const int ei = find_env(b.pre + PRE_INTERP * (b.nenv + 1), b.nenv, item);
-  const EnvView &e = b.envs[ei];
+  const EnvView &e = b.env(ei);
   const FrameF fr = env_frame(e, s);
   const int local = item - b.pre[PRE_INTERP * (b.nenv + 1) + ei];
   float *part = (e.wrench != nullptr && pass == b.mdf - 1) ? e.partials : nullptr;
   if (!UNI && e.rot) {
     if (pass > 0)
-      interp_item<WG, true, true>(e, e.b[0], fr, local, tid, part);
+      interp_item<WG, true, true>(e, e.b[b.set], fr, local, tid, part);
     else
-      interp_item<WG, true, false>(e, e.b[0], fr, local, tid, part);
+      interp_item<WG, true, false>(e, e.b[b.set], fr, local, tid, part);
   } else {
     if (pass > 0)
-      interp_item<WG, false, true>(e, e.b[0], fr, local, tid, part);
+      interp_item<WG, false, true>(e, e.b[b.set], fr, local, tid, part);
     else
-      interp_item<WG, false, false>(e, e.b[0], fr, local, tid, part);
+      interp_item<WG, false, false>(e, e.b[b.set], fr, local, tid, part);
   }
 }
 
-// add: on top of the earlier passes' force. final: the step's last spreading pass; its first item per environment also
-// sums the wrench partials.
+// add: on top of the earlier passes' force. final: the step's last spreading
+// pass, whose first item per environment also sums the wrench.
+template <int NT>
 __device__ inline void phase_spread(const BatchArgs &b, int s, bool final_pass, bool add, int item, const int *s_pre,
                                     int tid) {
   const int ei = find_env(s_pre, b.nenv, item);
-  const EnvView &e = b.envs[ei];
-  const int local = item - s_pre[ei];
+  const EnvView &e = b.env(ei);
+  const int local = uniform_i(item - s_pre[ei]);
   if (final_pass && local == 0 && e.wrench != nullptr)
-    wrench_sum<WG>(e.partials, e.n, e.wrench + (size_t)8 * s, tid);
-  spread_item<WG, false>(e, e.b[0], local, tid, e.gfix, add);
+    wrench_sum<NT>(e.partials, e.n, e.wrench + (size_t)8 * s, tid);
+  spread_item<NT, false>(e, e.b[b.set], local, tid, e.gfix, add);
 }
 
 // Collide item -> (environment, logical block); 512 threads as e.bx x e.by.
@@ -256,7 +272,7 @@ __device__ inline void phase_collide(const BatchArgs &b, const EnvView *__restri
   const int lb = item - pre[pos];
   const int cur = env_cur(e, s);
   const int tx = tid % e.bx, ty = tid / e.bx;
-  collide_item<K>(e, fr, cur, lb, tx, ty);
+  collide_item<K>(e, b.set, fr, cur, lb, tx, ty);
 }
 
 // Collide items handed out in launch order by a device-wide ticket counter
@@ -277,9 +293,9 @@ __device__ inline void collide_queue(const BatchArgs &b, int s, int tid) {
     if (item >= total) break;  // the same value in every thread
     if (tid == 0) s_ticket[k ^ 1] = (int)atomicAdd(&b.bar[BAR_QUEUE], 1u);
     const int pos = find_env(pre, b.nenv, item);
-    const EnvView &e = b.envs[b.corder[pos]];
+    const EnvView &e = b.env(b.corder[pos]);
     const int tx = tid % e.bx, ty = tid / e.bx;
-    collide_item<UNI ? 0 : -1>(e, env_frame(e, s), env_cur(e, s), item - pre[pos], tx, ty);
+    collide_item<UNI ? 0 : -1>(e, 0, env_frame(e, s), env_cur(e, s), item - pre[pos], tx, ty);
     __syncthreads();  // the next ticket is visible; this one was read by every thread
   }
 }
@@ -292,22 +308,23 @@ __device__ inline void collide_queue(const BatchArgs &b, int s, int tid) {
 __global__ void __launch_bounds__(kCgWG) kb_cg_init(BatchArgs b, int s) {
   const int *pre = b.pre + PRE_CG * (b.nenv + 1);
   const int ei = find_env(pre, b.nenv, blockIdx.x);
-  const EnvView &e = b.envs[ei];
+  const EnvView &e = b.env(ei);
   const FrameF fr = env_frame(e, s);
   if (e.rot)
-    cg_init_item<true>(e, e.b[0], fr, blockIdx.x - pre[ei]);
+    cg_init_item<true>(e, e.b[b.set], fr, blockIdx.x - pre[ei]);
   else
-    cg_init_item<false>(e, e.b[0], fr, blockIdx.x - pre[ei]);
+    cg_init_item<false>(e, e.b[b.set], fr, blockIdx.x - pre[ei]);
 }
 
 // Spreading of CG step j's search direction into each environment's gcg.
-__global__ void __launch_bounds__(WG) kb_spread_cg(BatchArgs b, int j) {
+__global__ void __launch_bounds__(BT) kb_spread_cg(BatchArgs b, int j) {
   __shared__ int s_pre[kMaxEnvs + 1];
-  const int tot = dynamic_prefix(b, kSpreadParts<WG>, s_pre, threadIdx.x);
+  const int tot = dynamic_prefix(b, kSpreadParts<BT>, s_pre, threadIdx.x);
   for (int item = blockIdx.x; item < tot; item += gridDim.x) {
     const int ei = find_env(s_pre, b.nenv, item);
-    const EnvView &e = b.envs[ei];
-    spread_item<WG, true>(e, e.b[0], item - s_pre[ei], threadIdx.x, e.gcg, false, cg_scal(e, 1, j), j == 0);
+    const EnvView &e = b.env(ei);
+    spread_item<BT, true>(e, e.b[b.set], uniform_i(item - s_pre[ei]), threadIdx.x, e.gcg, false, cg_scal(e, 1, j),
+                          j == 0);
   }
 }
 
@@ -316,21 +333,23 @@ __global__ void __launch_bounds__(WG) kb_cg_apply(BatchArgs b, int j) {
   const int *pre = b.pre + PRE_INTERP * (b.nenv + 1);
   const int item = xcd_item(blockIdx.x, gridDim.x);
   const int ei = find_env(pre, b.nenv, item);
-  cg_apply_item(b.envs[ei], b.envs[ei].b[0], item - pre[ei], threadIdx.x, j);
+  cg_apply_item(b.env(ei), b.env(ei).b[b.set], item - pre[ei], threadIdx.x, j);
 }
 
 // Grid: the total of PRE_CG.
 __global__ void __launch_bounds__(kCgWG) kb_cg_update(BatchArgs b, int s, int j, int last) {
   const int *pre = b.pre + PRE_CG * (b.nenv + 1);
   const int ei = find_env(pre, b.nenv, blockIdx.x);
-  const EnvView &e = b.envs[ei];
-  cg_update_item(e, e.b[0], env_frame(e, s), blockIdx.x - pre[ei], j, last != 0);
+  const EnvView &e = b.env(ei);
+  cg_update_item(e, e.b[b.set], env_frame(e, s), blockIdx.x - pre[ei], j, last != 0);
 }
 
 // ------------------------------------------------------ per-phase kernels --
-__global__ void __launch_bounds__(WG) kb_skin(BatchArgs b, int s) { phase_skin(b, s, blockIdx.x, threadIdx.x); }
+// The first step's skinning and binning; each other step's run beside the
+// interpolation and the last spreading of the step before it.
+__global__ void __launch_bounds__(WG) kb_skin(BatchArgs b) { phase_skin(b, 0, b.set, blockIdx.x, threadIdx.x); }
 
-__global__ void __launch_bounds__(WG) kb_active(BatchArgs b) { phase_active(b, blockIdx.x, threadIdx.x); }
+__global__ void __launch_bounds__(WG) kb_active(BatchArgs b) { phase_active(b, b.set, blockIdx.x, threadIdx.x); }
 
 template <bool UNI>
 __global__ void __launch_bounds__(WG) kb_macro(BatchArgs b, int s) {
@@ -339,18 +358,34 @@ __global__ void __launch_bounds__(WG) kb_macro(BatchArgs b, int s) {
   for (int item = w.first; item < w.end; item += w.step) phase_macro<UNI, true>(b, s, item, s_pre, threadIdx.x);
 }
 
+// Grid: every environment's interpolation items (each XCD takes consecutive
+// ones, the markers of a few environments, so its L2 holds their band macros),
+// after nskin workgroups that skin the next step's markers (0 or all of
+// PRE_SKIN).
 template <bool UNI>
-__global__ void __launch_bounds__(WG) kb_interp(BatchArgs b, int s, int pass) {
-  // grid = every environment's interpolation items; each XCD takes consecutive
-  // items (the markers of a few environments), so its L2 holds their band macros
-  phase_interp<UNI>(b, s, pass, xcd_item(blockIdx.x, gridDim.x), threadIdx.x);
+__global__ void __launch_bounds__(WG) kb_interp(BatchArgs b, int s, int pass, int nskin) {
+  const int blk = (int)blockIdx.x - nskin;
+  if (blk < 0)
+    phase_skin(b, s + 1, b.set ^ 1, blockIdx.x, threadIdx.x);
+  else
+    phase_interp<UNI>(b, s, pass, xcd_item(blk, gridDim.x - nskin), threadIdx.x);
 }
 
-__global__ void __launch_bounds__(WG) kb_spread(BatchArgs b, int s, int final_pass, int add) {
+// nbin workgroups that bin the next step's tiles (0, or items of PRE_ACTIVE, WG
+// tiles each by BT threads in two halves), then the spreading.
+__global__ void __launch_bounds__(BT) kb_spread(BatchArgs b, int s, int final_pass, int add, int nbin) {
   __shared__ int s_pre[kMaxEnvs + 1];
-  const int tot = dynamic_prefix(b, kSpreadParts<WG>, s_pre, threadIdx.x);
-  for (int item = blockIdx.x; item < tot; item += gridDim.x)
-    phase_spread(b, s, final_pass != 0, add != 0, item, s_pre, threadIdx.x);
+  const int blk = (int)blockIdx.x - nbin;
+  if (blk < 0) {
+    const int item = blockIdx.x, ei = find_env(b.pre + PRE_ACTIVE * (b.nenv + 1), b.nenv, item);
+    const EnvView &e = b.env(ei);
+    const int local = item - b.pre[PRE_ACTIVE * (b.nenv + 1) + ei];
+    for (int h = 0; h < WG / BT; ++h) active_item<BT>(e, e.b[b.set ^ 1], WG / BT * local + h, threadIdx.x);
+    return;
+  }
+  const int tot = dynamic_prefix(b, kSpreadParts<BT>, s_pre, threadIdx.x);
+  for (int item = blk; item < tot; item += gridDim.x - nbin)
+    phase_spread<BT>(b, s, final_pass != 0, add != 0, item, s_pre, threadIdx.x);
 }
 
 // Collide items item0 .. item0 + gridDim.x - 1, all of environments of kind
@@ -450,12 +485,12 @@ __global__ void __launch_bounds__(WG, 6) kb_persistent(BatchArgs b, int nsteps) 
   for (int s = 0; s < nsteps; ++s) {
     {
       const int tid = phase_tid(), blk = phase_blk(), grid = phase_grid();
-      for (int item = blk; item < b.tot[PRE_SKIN]; item += grid) phase_skin(b, s, item, tid);
+      for (int item = blk; item < b.tot[PRE_SKIN]; item += grid) phase_skin(b, s, 0, item, tid);
     }
     if (!grid_sync(b)) return;
     {
       const int tid = phase_tid(), blk = phase_blk(), grid = phase_grid();
-      for (int item = blk; item < b.tot[PRE_ACTIVE]; item += grid) phase_active(b, item, tid);
+      for (int item = blk; item < b.tot[PRE_ACTIVE]; item += grid) phase_active(b, 0, item, tid);
     }
     if (!grid_sync(b)) return;
     {
@@ -473,7 +508,7 @@ __global__ void __launch_bounds__(WG, 6) kb_persistent(BatchArgs b, int nsteps) 
     for (int pass = 0; pass < b.mdf; ++pass) {
       if (pass > 0) {
         const int tid = phase_tid(), blk = phase_blk(), grid = phase_grid();
-        for (int item = blk; item < tot; item += grid) phase_spread(b, s, false, pass > 1, item, s_pre, tid);
+        for (int item = blk; item < tot; item += grid) phase_spread<WG>(b, s, false, pass > 1, item, s_pre, tid);
         if (!grid_sync(b)) return;
       }
       {
@@ -485,7 +520,7 @@ __global__ void __launch_bounds__(WG, 6) kb_persistent(BatchArgs b, int nsteps) 
     }
     {
       const int tid = phase_tid(), blk = phase_blk(), grid = phase_grid();
-      for (int item = blk; item < tot; item += grid) phase_spread(b, s, true, b.mdf > 1, item, s_pre, tid);
+      for (int item = blk; item < tot; item += grid) phase_spread<WG>(b, s, true, b.mdf > 1, item, s_pre, tid);
     }
     if (!grid_sync(b)) return;
     {

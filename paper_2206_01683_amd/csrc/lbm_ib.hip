@@ -1493,6 +1493,7 @@ BatchArgs batch_args(const lbm_batch *b) {
   a.corder = b->d_pre + 4 * (b->nenv + 1);
   for (int q = 0; q < 4; ++q) a.tot[q] = b->tot[q];
   a.mdf = b->mdf;
+  a.set = 0;
   a.bar = b->d_bar;
   return a;
 }
@@ -1515,9 +1516,12 @@ void batch_collide(const lbm_batch *b, const BatchArgs &a, int s) {
     if (b->kind_n[k] > 0) table[k](a, s, b->kind_lo[k], b->kind_n[k], b->stream);
 }
 
+// Each step's skinning and binning run beside the interpolation and the last
+// spreading of the step before; the body sets alternate so that the last step
+// uses set 0 (as in step_beside_t).
 template <bool UNI>
 lbm_status batch_enqueue_t(lbm_batch *b, int nsteps, int mode) {
-  const BatchArgs a = batch_args(b);
+  BatchArgs a = batch_args(b);
   if (mode == LBM_BATCH_PERSISTENT) {
     kb_persistent<UNI><<<b->persistent_grid[UNI ? 1 : 0], WG, 0, b->stream>>>(a, nsteps);
     return launched();
@@ -1525,33 +1529,38 @@ lbm_status batch_enqueue_t(lbm_batch *b, int nsteps, int mode) {
   int cap_items = 0;
   for (int e = 0; e < b->nenv; ++e) cap_items += b->views[e].cap;
   const int gdyn = std::max(8, std::min(4 * cap_items, 4096));
+  int nskin = 0, nbin = 0;  // workgroups for the next step
   // interpolation branches per environment only on rotation
-  auto interp = [&](const BatchArgs &args, int s, int pass) {
+  auto interp = [&](int s, int pass) {
+    const int front = pass == 0 ? nskin : 0, grid = front + b->tot[PRE_INTERP];
     if (UNI || b->still)
-      kb_interp<true><<<b->tot[PRE_INTERP], WG, 0, b->stream>>>(args, s, pass);
+      kb_interp<true><<<grid, WG, 0, b->stream>>>(a, s, pass, front);
     else
-      kb_interp<false><<<b->tot[PRE_INTERP], WG, 0, b->stream>>>(args, s, pass);
+      kb_interp<false><<<grid, WG, 0, b->stream>>>(a, s, pass, front);
   };
-  for (int s = 0; s < nsteps; ++s) {
-    kb_skin<<<b->tot[PRE_SKIN], WG, 0, b->stream>>>(a, s);
-    kb_active<<<b->tot[PRE_ACTIVE], WG, 0, b->stream>>>(a);
+  a.set = (nsteps - 1) & 1;
+  kb_skin<<<b->tot[PRE_SKIN], WG, 0, b->stream>>>(a);
+  kb_active<<<b->tot[PRE_ACTIVE], WG, 0, b->stream>>>(a);
+  for (int s = 0; s < nsteps; ++s, a.set ^= 1) {
+    nskin = s + 1 < nsteps ? b->tot[PRE_SKIN] : 0;
+    nbin = s + 1 < nsteps ? b->tot[PRE_ACTIVE] : 0;
     kb_macro<UNI><<<gdyn, WG, 0, b->stream>>>(a, s);
     if (b->implicit) {  // mdf = conjugate-gradient steps
-      interp(a, s, 0);
+      interp(s, 0);
       kb_cg_init<<<b->tot_cg, kCgWG, 0, b->stream>>>(a, s);
       for (int j = 0; j < b->mdf; ++j) {
         const bool last = j == b->mdf - 1;
-        kb_spread_cg<<<gdyn, WG, 0, b->stream>>>(a, j);
+        kb_spread_cg<<<gdyn, BT, 0, b->stream>>>(a, j);
         kb_cg_apply<<<b->tot[PRE_INTERP], WG, 0, b->stream>>>(a, j);
         kb_cg_update<<<b->tot_cg, kCgWG, 0, b->stream>>>(a, s, j, last ? 1 : 0);
       }
     } else {
       for (int pass = 0; pass < b->mdf; ++pass) {
-        if (pass > 0) kb_spread<<<gdyn, WG, 0, b->stream>>>(a, s, 0, pass > 1);
-        interp(a, s, pass);
+        if (pass > 0) kb_spread<<<gdyn, BT, 0, b->stream>>>(a, s, 0, pass > 1, 0);
+        interp(s, pass);
       }
     }
-    kb_spread<<<gdyn, WG, 0, b->stream>>>(a, s, 1, !b->implicit && b->mdf > 1);
+    kb_spread<<<nbin + gdyn, BT, 0, b->stream>>>(a, s, 1, !b->implicit && b->mdf > 1, nbin);
     batch_collide(b, a, s);
     lbm_status st = launched();
     if (st != LBM_OK) return st;
