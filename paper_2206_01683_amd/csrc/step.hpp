@@ -87,11 +87,13 @@ inline int bulk_blocks(const EnvView &e) { return (int)(((size_t)e.g.nx * e.g.ny
 // nodes beyond it (the source node of a face node is its inward neighbour):
 // along z the neighbouring face plane, along x and y those of a last tile that
 // is one node wide (a dimension of 8k + 1). The plane's populations are pulled
-// first, so that their latency overlaps the spreading. add: the force starts
-// from gfix (earlier forcing passes).
+// first, so that their latency overlaps the spreading. force: kForceAdd, the
+// force starts from gfix (earlier forcing passes); kForceKeep, it is also
+// written there (a recorded step).
+enum { kForceAdd = 1, kForceKeep = 2 };
 template <class S, bool XPER, bool ROT, bool YZ, bool TRT>
 __device__ inline void band_item(const EnvView &e, const BodySet &bs, const FrameF &fr, int cur, int item, int tid,
-                                 bool add, SpreadLds<3> &s) {
+                                 int force, SpreadLds<3> &s) {
   const GridArgs &g = e.g;
   const int slot = item >> 3, plane = item & 7;
   const TileAt t = active_of(bs, slot);
@@ -107,9 +109,10 @@ __device__ inline void band_item(const EnvView &e, const BodySet &bs, const Fram
     own = source_here(c);
     if (own) collide_pull<S, XPER, YZ>(e, cur, c, f);
   }
-  const gmem<unsigned long long> *gp = (const gmem<unsigned long long> *)e.gfix + (size_t)slot * 1536 + plane * 64;
-  if (tid < 192) (&s.acc[0][0])[tid] = add ? gp[512 * (tid >> 6) + (tid & 63)] : 0ull;
+  gmem<unsigned long long> *gp = (gmem<unsigned long long> *)e.gfix + (size_t)slot * 1536 + plane * 64;
+  if (tid < 192) (&s.acc[0][0])[tid] = (force & kForceAdd) ? gp[512 * (tid >> 6) + (tid & 63)] : 0ull;
   spread_plane<false>(e, bs, t, plane, tid, s);
+  if ((force & kForceKeep) && tid < 192) gp[512 * (tid >> 6) + (tid & 63)] = (&s.acc[0][0])[tid];
   auto finish = [&](const CellAt &cc, float ff[Q]) {
     const int lc = (cc.xs & 7) | ((cc.ys & 7) << 3);
     collide_finish<S, XPER, ROT, YZ, TRT>(e, fr, cur, cc, ff, from_fix(s.acc[0][lc]), from_fix(s.acc[1][lc]),
@@ -208,7 +211,7 @@ __global__ void __launch_bounds__(BT, 4) k_step_interp(EnvView e, FrameF fr, int
 // (null: none), active_items for the next step's binning (next.pose null: none).
 // The bulk starts at block first_bulk.
 template <class S, bool XPER, bool ROT, bool YZ, bool TRT>
-__global__ void __launch_bounds__(BT, 4) k_step_band(EnvView e, FrameF fr, int cur, int nt, int add, float *wrench,
+__global__ void __launch_bounds__(BT, 4) k_step_band(EnvView e, FrameF fr, int cur, int nt, int force, float *wrench,
                                                      NextStep next, int first_bulk, int gap) {
   const int tid = threadIdx.x;
   int blk = blockIdx.x;
@@ -219,7 +222,7 @@ __global__ void __launch_bounds__(BT, 4) k_step_band(EnvView e, FrameF fr, int c
     __shared__ SpreadLds<3> s;
     const int items = 8 * n_active_of(e, e.b[0]);
     for (int item = blk; item < items; item += nt)
-      band_item<S, XPER, ROT, YZ, TRT>(e, e.b[0], fr, cur, item, tid, add != 0, s);
+      band_item<S, XPER, ROT, YZ, TRT>(e, e.b[0], fr, cur, item, tid, force, s);
   } else if (blk < nt + nw) {
     wrench_sum<BT>(e.partials, e.n, wrench, tid);
   } else if (blk < nt + nw + nb) {
