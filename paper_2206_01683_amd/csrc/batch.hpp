@@ -19,7 +19,7 @@
 //                    (a timeout sets a status bit and every workgroup exits).
 //                    F32 storage and direct forcing only.
 // The marker phases don't run beside the collides as a lone lattice's do
-// (step.hpp): over many lattices they fill the chip, and the band, 9 % of the
+// (step.hpp): over many lattices they fill the chip, and the band, 3 % of the
 // cells of lattices this small, is read and written in 32-byte rows whose lines
 // a collide beside them drives out of L2 (48 lattices of 0.3 to 1.3 million
 // cells: macros 93 and band collides 282 us alone, 194 and 585 us more beside).
