@@ -466,10 +466,7 @@ lbm_status lbm_body_forces(lbm_ctx *c, const lbm_markers *m, const double *cente
 
 /* Synchronize the stream and report device-side guards: LBM_ERR_UNSTABLE,
  * LBM_ERR_MARKER_RANGE, LBM_ERR_CAPACITY, LBM_ERR_ARG (a bone index out of
- * range), LBM_ERR_DEVICE (a barrier of the one-launch step waited past its
- * limit, which only a device shared with work that never yields can cause;
- * the steps since the last check are then void), or LBM_OK. Clears the
- * guards. */
+ * range), or LBM_OK. Clears the guards. */
 lbm_status lbm_check(lbm_ctx *c);
 
 /* Measurement hook. enable != 0: every later step brackets its two phases
@@ -512,7 +509,7 @@ typedef struct {
   int32_t rotating;         /* 0: every frame has omega = alpha = 0 (cheaper arithmetic); 1: general */
 } lbm_env;
 
-enum { LBM_BATCH_PHASES = 0,     /* one launch per phase per step */
+enum { LBM_BATCH_PHASES = 0,     /* a launch per phase per step, the next step's skinning and binning beside */
        LBM_BATCH_PERSISTENT = 1  /* one launch for all steps, device-wide barriers between phases */
 };
 
