@@ -256,7 +256,7 @@ __device__ inline void phase_spread(const BatchArgs &b, int s, bool final_pass, 
   const EnvView &e = b.env(ei);
   const int local = uniform_i(item - s_pre[ei]);
   if (final_pass && local == 0 && e.wrench != nullptr)
-    wrench_sum<NT>(e.partials, e.n, e.wrench + (size_t)8 * s, tid);
+    wrench_sum<NT>(e.partials, e.n, false, e.wrench + (size_t)8 * s, tid);
   spread_item<NT, false>(e, e.b[b.set], local, tid, e.gfix, add);
 }
 

@@ -455,8 +455,10 @@ __device__ inline void macro_item(const EnvView &e, const BodySet &bs, const Fra
 // current immersed force, u = u* + (I + [omega]x)^-1 g / (2 rho), and
 // F_k += 2 alpha rho_k (U_k - U_k^interp).
 // The record carries this pass's F increment times dV (spreading adds each
-// pass into the step's force). With partials != nullptr: the marker's share of
-// the fluid's force, torque about the frame origin and power, partials[k][8].
+// pass into the step's force). With partials != nullptr: the markers' shares of
+// the fluid's force, torque about the frame origin and power, eight floats each:
+// summed over kShareMk consecutive markers, a row of the partials each
+// (interp_item), or a row per marker (interp_wave).
 // Node weight delta = wx (wy wz), the product the spreading uses. The 64-node
 // sums add each x-row of four nodes in order, then the 16 rows by a butterfly,
 // in both forms below: the same bits.
@@ -494,12 +496,15 @@ __device__ inline float stencil_weight(const float X[3], const int base[3], int 
   return peskin4(x - (float)(b + (q & 3)));
 }
 
+constexpr int kShareMk = 16;  // markers per row of the wrench partials
+__device__ __host__ inline int share_rows(int n) { return (n + kShareMk - 1) / kShareMk; }
+
 // What one lane does with marker k's sums: force, record and wrench share
 // (the record's weights are stored by the caller).
 template <bool MDF>
 __device__ inline void force_marker(const EnvView &e, const BodySet &bs, const FrameF &fr, int k, float sr,
                                     const float Ui[3], const float Xk[3], const float Uk[3], float dvk,
-                                    const int base[3], float *partials) {
+                                    const int base[3], float part[7]) {
   // multiply-adds fuse only within one expression, never across statements,
   // so every kernel that inlines this rounds its outputs identically
 #pragma clang fp contract(on)
@@ -540,13 +545,25 @@ __device__ inline void force_marker(const EnvView &e, const BodySet &bs, const F
   }
   *(gmem<vfloat4> *)(r + 12) = vfloat4{__int_as_float(base[0]), __int_as_float(base[1]), __int_as_float(base[2]), 0.f};
   *(gmem<vfloat4> *)(r + 16) = vfloat4{inc[0] * dvk, inc[1] * dvk, inc[2] * dvk, 0.f};
-  if (partials == nullptr) return;
   // fluid on body: -F dV; torque (X - x0) x (-F dV); power F.U dV
   const float rx = Xk[0] - fr.org[0], ry = Xk[1] - fr.org[1], rz = Xk[2] - fr.org[2];
-  gmem<vfloat4> *p = (gmem<vfloat4> *)(partials + 8 * (size_t)k);
-  p[0] = vfloat4{-fd[0], -fd[1], -fd[2], -(ry * fd[2] - rz * fd[1])};
-  p[1] = vfloat4{-(rz * fd[0] - rx * fd[2]), -(rx * fd[1] - ry * fd[0]),
-                 fd[0] * Uk[0] + fd[1] * Uk[1] + fd[2] * Uk[2], 0.f};
+  part[0] = -fd[0];
+  part[1] = -fd[1];
+  part[2] = -fd[2];
+  part[3] = -(ry * fd[2] - rz * fd[1]);
+  part[4] = -(rz * fd[0] - rx * fd[2]);
+  part[5] = -(rx * fd[1] - ry * fd[0]);
+  part[6] = fd[0] * Uk[0] + fd[1] * Uk[1] + fd[2] * Uk[2];
+}
+
+// Column `col` of row r of the wrench partials, added in marker order: share(q)
+// is that of the row's q-th marker, zero past the last one.
+template <class F>
+__device__ inline float share_sum(F share) {
+  float sum = 0.f;
+#pragma unroll
+  for (int q = 0; q < kShareMk; ++q) sum += share(q);
+  return sum;
 }
 
 // Markers NT / 16 a workgroup, from the band macros.
@@ -630,11 +647,23 @@ __device__ inline void interp_item(const EnvView &e, const BodySet &bs, const Fr
   sx = group16_sum(sx);
   sy = group16_sum(sy);
   sz = group16_sum(sz);
+  float part[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (live) {
     if (sub < 12) ((gmem<float> *)e.rec)[(size_t)k * REC + sub] = w;
     const float Ui[3] = {sx, sy, sz};
-    if (sub == 0) force_marker<MDF>(e, bs, fr, k, sr, Ui, Xk, Uk, dvk, base, partials);
+    if (sub == 0) force_marker<MDF>(e, bs, fr, k, sr, Ui, Xk, Uk, dvk, base, part);
   }
+  if (partials == nullptr) return;  // uniform over the workgroup
+  constexpr int ROWS = NT / 16 / kShareMk;
+  __shared__ float s_part[NT / 16][8];
+  if (sub == 0)
+    for (int q = 0; q < 7; ++q) s_part[tid >> 4][q] = part[q];
+  __syncthreads();
+  const int row = item * ROWS + (tid >> 3), col = tid & 7;
+  if (tid < 8 * ROWS && row < share_rows(n))
+    ((gmem<float> *)partials)[(size_t)row * 8 + col] =
+        col < 7 ? share_sum([&](int q) { return s_part[(tid >> 3) * kShareMk + q][col]; }) : 0.f;
+  __syncthreads();  // s_part is reused by the next item
 }
 
 // Value of lane i of this lane's group of four (DPP quad permute).
@@ -704,7 +733,15 @@ __device__ inline void interp_wave(const EnvView &e, const BodySet &bs, const Fr
     s[c] += row_turn<4>(s[c]);
   }
   const float Ui[3] = {s[1], s[2], s[3]};
-  if (lane == 0) force_marker<false>(e, bs, fr, k, s[0], Ui, Xk, Uk, dvk, base, partials);
+  if (lane == 0) {
+    float part[7];
+    force_marker<false>(e, bs, fr, k, s[0], Ui, Xk, Uk, dvk, base, part);
+    if (partials != nullptr) {
+      gmem<vfloat4> *p = (gmem<vfloat4> *)(partials + 8 * (size_t)k);
+      p[0] = vfloat4{part[0], part[1], part[2], part[3]};
+      p[1] = vfloat4{part[4], part[5], part[6], 0.f};
+    }
+  }
 }
 
 template <int NT = WG>
@@ -713,26 +750,40 @@ __device__ __host__ inline int interp_items(int n) {
 }
 __device__ __host__ inline int wave_items(int n) { return (n + kWavePer - 1) / kWavePer; }
 
-// Wrench of the step: the markers' shares in a fixed order by NT threads, as
-// WG / 8 interleaved sums whatever NT (so that every kernel gives the same
-// bits).
+// Wrench of the step by NT threads, in a fixed order whatever NT and the kernel:
+// the markers' shares by rows of kShareMk (partials holds the rows, or by_marker
+// the shares), the rows as WG / 8 interleaved sums and those one after the other,
+// from the rows on in double precision, so that the rounding doesn't grow with
+// the number of markers. One workgroup does it, in the launch that the step ends
+// with: added marker by marker it was that launch's tail (12,000 markers on
+// 384x192x192 in launches of their own: 553 us a step, 540 by rows; 200,000 on
+// 192x96x96: 515 and 283).
 template <int NT>
-__device__ inline void wrench_sum(const float *__restrict__ partials, int n, float *__restrict__ wrench, int tid) {
-  __shared__ float s_red[WG];
+__device__ inline void wrench_sum(const float *__restrict__ partials, int n, bool by_marker,
+                                  float *__restrict__ wrench, int tid) {
+  __shared__ double s_red[WG];
+  const gmem<float> *p = (const gmem<float> *)partials;
+  const int rows = share_rows(n);
   for (int q = tid; q < WG; q += NT) {
     const int col = q & 7;
-    float acc = 0.f;
-    if (col < 7) {
+    double acc = 0.0;
+    if (col < 7 && by_marker) {
+      for (int r = q >> 3; r < rows; r += WG / 8)
+        acc += share_sum([&](int j) {
+          const int k = r * kShareMk + j;
+          return k < n ? p[(size_t)k * 8 + col] : 0.f;
+        });
+    } else if (col < 7) {
 #pragma unroll 8
-      for (int k = q >> 3; k < n; k += WG / 8) acc += ((const gmem<float> *)partials)[(size_t)k * 8 + col];
+      for (int r = q >> 3; r < rows; r += WG / 8) acc += p[(size_t)r * 8 + col];
     }
     s_red[q] = acc;
   }
   __syncthreads();
   if (tid < 8) {
-    float sum = 0.f;
+    double sum = 0.0;
     for (int r2 = 0; r2 < WG / 8; ++r2) sum += s_red[r2 * 8 + tid];
-    wrench[tid] = tid < 7 ? sum : 0.f;
+    wrench[tid] = tid < 7 ? (float)sum : 0.f;
   }
   __syncthreads();
 }
@@ -888,7 +939,7 @@ __global__ void __launch_bounds__(BT) k_interp(EnvView e, FrameF fr, float *part
 
 // wrench != nullptr: workgroup 0 first sums the interpolation partials.
 __global__ void __launch_bounds__(BT) k_spread(EnvView e, float *wrench, int add) {
-  if (blockIdx.x == 0 && wrench != nullptr) wrench_sum<BT>(e.partials, e.n, wrench, threadIdx.x);
+  if (blockIdx.x == 0 && wrench != nullptr) wrench_sum<BT>(e.partials, e.n, false, wrench, threadIdx.x);
   const int items = kSpreadParts<BT> * n_active_of(e, e.b[0]);
   for (int item = blockIdx.x; item < items; item += gridDim.x)
     spread_item<BT, false>(e, e.b[0], item, threadIdx.x, e.gfix, add != 0);
@@ -1188,10 +1239,14 @@ __device__ inline void cg_update_item(const EnvView &e, const BodySet &bs, const
     }
     return;
   }
-  if (k < n) {
+  __shared__ float s_part[7][kCgWG + 1];  // the wrench rows, as interp_item
 #pragma unroll
-    for (int qd = 0; qd < 7; ++qd) e.partials[8 * (size_t)k + qd] = part[qd];
-  }
+  for (int q = 0; q < 7; ++q) s_part[q][threadIdx.x] = part[q];
+  __syncthreads();
+  const int row = item * (kCgWG / kShareMk) + (int)(threadIdx.x >> 3), col = threadIdx.x & 7;
+  if (threadIdx.x < 8 * (kCgWG / kShareMk) && row < share_rows(n))
+    e.partials[8 * (size_t)row + col] =
+        col < 7 ? share_sum([&](int q) { return s_part[col][(threadIdx.x >> 3) * kShareMk + q]; }) : 0.f;
 }
 
 template <bool ROT>

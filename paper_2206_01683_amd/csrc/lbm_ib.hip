@@ -127,7 +127,8 @@ Layout layout(const lbm_params *p) {
   L.X2 = take(sizeof(float) * 3 * (size_t)L.maxm);
   L.U2 = take(sizeof(float) * 3 * (size_t)L.maxm);
   L.list = take(sizeof(int) * list_entries(p) * (size_t)L.maxm);
-  L.partials = take(sizeof(float) * 8 * (size_t)L.maxm);
+  // wrench partials: a row per kShareMk markers, or per marker where few (kDirectMarkers)
+  L.partials = take(sizeof(float) * 8 * (size_t)std::max(share_rows(L.maxm), std::min(L.maxm, kDirectMarkers)));
   L.macro = take(sizeof(float) * 4 * 512 * (size_t)L.cap);
   L.gbuf = take(sizeof(unsigned long long) * 3 * 512 * (size_t)L.cap);
   L.rec = take(sizeof(float) * REC * (size_t)L.maxm);
@@ -460,12 +461,12 @@ void step_interp_kernels(const EnvView &e, const FrameF &fr, int cur, bool rot, 
 }
 
 template <class S, bool TRT>
-void step_band_kernels(const EnvView &e, const FrameF &fr, int cur, bool rot, int force, float *wrench, NextStep next,
-                       int first_bulk, hipStream_t s) {
+void step_band_kernels(const EnvView &e, const FrameF &fr, int cur, bool rot, int force, float *wrench, int by_marker,
+                       NextStep next, int first_bulk, hipStream_t s) {
   const int nt = std::min(8 * e.cap, kBandWorkgroups);
   const StepLaunch l = step_launch<S>(e, nt + (wrench ? 1 : 0) + (next.pose ? active_items<BT>(e) : 0), first_bulk,
-                                      bulk_blocks(e) - first_bulk, sizeof(SpreadLds<3>) + 2 * 1024);
-#define LBM_STEP_ARGS (e, fr, cur, nt, force, wrench, next, l.first_bulk, l.gap)
+                                      bulk_blocks(e) - first_bulk, sizeof(SpreadLds<3>) + 4 * 1024);
+#define LBM_STEP_ARGS (e, fr, cur, nt, force, wrench, by_marker, next, l.first_bulk, l.gap)
   LBM_STEP_FORM(k_step_band, l.grid, BT, l.lds, s);
 #undef LBM_STEP_ARGS
 }
@@ -635,7 +636,8 @@ lbm_status step_beside_t(lbm_ctx *c, const lbm_markers *m, const float *poses, c
     } else if ((st = launch_passes(c, e, fr, rot, wr != nullptr)) != LBM_OK) {
       return st;
     }
-    step_band_kernels<S, TRT>(e, fr, c->cur, rot, spread_adds(c) ? kForceAdd : 0, wr, next, done, c->stream);
+    step_band_kernels<S, TRT>(e, fr, c->cur, rot, spread_adds(c) ? kForceAdd : 0, wr, macros ? 0 : 1, next, done,
+                              c->stream);
     if ((st = launched()) != LBM_OK) return st;
     prof_mark(c, 2);
     prof_step(c, chained);
@@ -1138,7 +1140,7 @@ lbm_status segment_record(lbm_ctx *c, const void *ckpt, void *const *ring, int32
       const int share = (int)((int64_t)bulk_blocks(e) * kBulkShare / 16);
       step_macro_kernels<StoreF32, false>(e, fr, 0, false, nl, next, share, c->stream);
       step_interp_kernels<StoreF32, false>(e, fr, 0, false, 0, wr ? e.partials : nullptr, next, share, share, c->stream);
-      step_band_kernels<StoreF32, false>(e, fr, 0, false, kForceKeep, wr, next, 2 * share, c->stream);
+      step_band_kernels<StoreF32, false>(e, fr, 0, false, kForceKeep, wr, 0, next, 2 * share, c->stream);
       if ((st = launched()) != LBM_OK) return st;
       continue;
     }

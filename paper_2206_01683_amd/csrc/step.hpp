@@ -208,11 +208,12 @@ __global__ void __launch_bounds__(BT, 4) k_step_interp(EnvView e, FrameF fr, int
 }
 
 // Marker workgroups: nt over the planes of the active tiles, one for the wrench
-// (null: none), active_items for the next step's binning (next.pose null: none).
+// (null: none; by_marker: from shares that k_step_interp took straight from the
+// populations), active_items for the next step's binning (next.pose null: none).
 // The bulk starts at block first_bulk.
 template <class S, bool XPER, bool ROT, bool YZ, bool TRT>
 __global__ void __launch_bounds__(BT, 4) k_step_band(EnvView e, FrameF fr, int cur, int nt, int force, float *wrench,
-                                                     NextStep next, int first_bulk, int gap) {
+                                                     int by_marker, NextStep next, int first_bulk, int gap) {
   const int tid = threadIdx.x;
   int blk = blockIdx.x;
   const int nw = wrench != nullptr ? 1 : 0, nb = next.pose != nullptr ? active_items<BT>(e) : 0;
@@ -224,7 +225,7 @@ __global__ void __launch_bounds__(BT, 4) k_step_band(EnvView e, FrameF fr, int c
     for (int item = blk; item < items; item += nt)
       band_item<S, XPER, ROT, YZ, TRT>(e, e.b[0], fr, cur, item, tid, force, s);
   } else if (blk < nt + nw) {
-    wrench_sum<BT>(e.partials, e.n, wrench, tid);
+    wrench_sum<BT>(e.partials, e.n, by_marker != 0, wrench, tid);
   } else if (blk < nt + nw + nb) {
     active_item<BT>(e, e.b[1], blk - nt - nw, tid);
   }
