@@ -174,8 +174,9 @@ __device__ inline bool collide_load(const EnvView &e, int cur, int lb, int tx, i
 // and the 27 stores of f*(n). TRT: the two-relaxation-time collision instead
 // of BGK (even and odd parts of f relax at omega+ and omega-, Guo's source
 // split the same way).
-// (gx, gy, gz): the immersed force density at the source node.
-template <class S, bool XPER, bool ROT, bool YZ = false, bool TRT = false>
+// (gx, gy, gz): the immersed force density at the source node. STREAM: the
+// stores are nontemporal (see stream_store).
+template <class S, bool XPER, bool ROT, bool YZ = false, bool TRT = false, bool STREAM = true>
 __device__ inline void collide_finish(const EnvView &e, const FrameF &fr, int cur, const CellAt &c, float f[Q],
                                       float gx, float gy, float gz) {
   // multiply-adds fused within a source expression only, so that this
@@ -271,12 +272,12 @@ __device__ inline void collide_finish(const EnvView &e, const FrameF &fr, int cu
       const float cF = cdot(i, Fx, Fy, Fz);
       const float even = w * (E * (Ah + 4.5f * cu * cu) + B) + (w * P) * (9.0f * cu * cF - 3.0f * uF);
       const float odd = (w * E) * (3.0f * cu) + (w * P) * (3.0f * cF);
-      S::store_dev(d + (size_t)i * g.ps, e.omt * f[i] + even + odd, i);
-      S::store_dev(d + (size_t)j * g.ps, e.omt * f[j] + even - odd, j);
+      S::template store_dev<STREAM>(d + (size_t)i * g.ps, e.omt * f[i] + even + odd);
+      S::template store_dev<STREAM>(d + (size_t)j * g.ps, e.omt * f[j] + even - odd);
     }
     {
       const float w = w_of(13);
-      S::store_dev(d + (size_t)13 * g.ps, e.omt * f[13] + w * (E * Ah + B) - (w * P) * 3.0f * uF, 13);
+      S::template store_dev<STREAM>(d + (size_t)13 * g.ps, e.omt * f[13] + w * (E * Ah + B) - (w * P) * 3.0f * uF);
     }
   } else {
     // h*_i = h_i - w+ (h+_i - heq+_i) - w- (h-_i - heq-_i) + (1 - w+/2) S+_i + (1 - w-/2) S-_i
@@ -293,13 +294,13 @@ __device__ inline void collide_finish(const EnvView &e, const FrameF &fr, int cu
       const float cF = cdot(i, Fx, Fy, Fz);
       const float even = w * (Ep * (Ah + 4.5f * cu * cu) + Bp) + (w * Pp) * (9.0f * cu * cF - 3.0f * uF);
       const float odd = (w * Em) * (3.0f * cu) + (w * Pm) * (3.0f * cF);
-      S::store_dev(d + (size_t)i * g.ps, a * f[i] + b * f[j] + even + odd, i);
-      S::store_dev(d + (size_t)j * g.ps, a * f[j] + b * f[i] + even - odd, j);
+      S::template store_dev<STREAM>(d + (size_t)i * g.ps, a * f[i] + b * f[j] + even + odd);
+      S::template store_dev<STREAM>(d + (size_t)j * g.ps, a * f[j] + b * f[i] + even - odd);
     }
     {
       const float w = w_of(13);
-      S::store_dev(d + (size_t)13 * g.ps, (1.0f - e.trt.wp) * f[13] + w * (Ep * Ah + Bp) - (w * Pp) * 3.0f * uF,
-                   13);
+      S::template store_dev<STREAM>(d + (size_t)13 * g.ps,
+                                    (1.0f - e.trt.wp) * f[13] + w * (Ep * Ah + Bp) - (w * Pp) * 3.0f * uF);
     }
   }
 }

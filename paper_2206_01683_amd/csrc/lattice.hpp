@@ -38,13 +38,23 @@ typedef float vfloat4 __attribute__((ext_vector_type(4)));  // float4 as a nativ
 // directly (rho - 1 = sum h, m = sum h c), so the rounding of a stored value
 // scales with |h| rather than with w_i; load / store convert to and from f
 // for the kernels that want f.
+// Populations are written nontemporal where a launch writes whole lines (STREAM):
+// nothing reads them before the next step.
+template <bool STREAM, class V, class P>
+__device__ inline void stream_store(V v, P p) {
+  if constexpr (STREAM)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+
 struct StoreF32 {
   using T = float;
   static constexpr int kind = 0;
   template <class P>
   __device__ static inline float load_dev(P p, int) { return *p; }
-  template <class P>
-  __device__ static inline void store_dev(P p, float h, int) { __builtin_nontemporal_store(h, p); }
+  template <bool STREAM, class P>
+  __device__ static inline void store_dev(P p, float h) { stream_store<STREAM>(h, p); }
   template <class P>
   __device__ static inline float load(P p, int i) { return w_of(i) + *p; }
   template <class P>
@@ -58,8 +68,8 @@ struct StoreF16 {
   static constexpr int kind = 1;
   template <class P>
   __device__ static inline float load_dev(P p, int) { return (float)(*p); }
-  template <class P>
-  __device__ static inline void store_dev(P p, float h, int) { __builtin_nontemporal_store((_Float16)h, p); }
+  template <bool STREAM, class P>
+  __device__ static inline void store_dev(P p, float h) { stream_store<STREAM>((_Float16)h, p); }
   template <class P>
   __device__ static inline float load(P p, int i) { return w_of(i) + (float)(*p); }
   template <class P>
@@ -82,8 +92,8 @@ struct StoreBF16 {
   }
   template <class P>
   __device__ static inline float load_dev(P p, int) { return to_f(*p); }
-  template <class P>
-  __device__ static inline void store_dev(P p, float h, int) { __builtin_nontemporal_store(to_h(h), p); }
+  template <bool STREAM, class P>
+  __device__ static inline void store_dev(P p, float h) { stream_store<STREAM>(to_h(h), p); }
   template <class P>
   __device__ static inline float load(P p, int i) { return w_of(i) + to_f(*p); }
   template <class P>
