@@ -422,28 +422,25 @@ bool beside_collide(const lbm_ctx *c) { return c->p.ib_workgroups >= 0; }
     }                                                                                       \
   } while (0)
 
-// The shape of one launch of a step: marker workgroups, bulk blocks from
-// first_bulk on, spacing and LDS reservation (see kGap); lds_own: the kernel's
-// own LDS.
+// The shape of one launch of a step: `front` marker workgroups, `bulk` blocks of
+// the collide and the LDS reservation (see kCapBlocks); lds_own: the kernel's own
+// LDS.
 struct StepLaunch {
-  int first_bulk, gap, grid;
+  int grid;
   size_t lds;
 };
 template <class S>
-StepLaunch step_launch(const EnvView &e, int front, int first_bulk, int bulk, size_t lds_own) {
-  const int groups = (front + 7) / 8;
-  const bool cap = S::kind == StoreF32::kind && bulk_blocks(e) >= kCapBlocks;
-  const size_t want = collide_lds<S>(dim3(BT));
-  const int gap = cap && bulk > 8 * kCapResident ? std::min(kGap, bulk / std::max(1, groups)) : 0;
-  return {first_bulk, gap, 8 * groups + bulk, cap && want > lds_own ? want - lds_own : 0};
+StepLaunch step_launch(const EnvView &e, int front, int bulk, size_t lds_own) {
+  const size_t want = S::kind == StoreF32::kind && bulk_blocks(e) >= kCapBlocks ? collide_lds<S>(dim3(BT)) : 0;
+  return {((front + 7) & ~7) + bulk, want > lds_own ? want - lds_own : 0};
 }
 
 template <class S, bool TRT>
 void step_macro_kernels(const EnvView &e, const FrameF &fr, int cur, bool rot, int nl, NextStep next, int bulk,
                         hipStream_t s) {
   const int nm = std::min(2 * e.cap, kMacroWorkgroups);
-  const StepLaunch l = step_launch<S>(e, nm + nl + (next.pose ? skin_items<BT>(e.n) : 0), 0, bulk, 5 * 1024);
-#define LBM_STEP_ARGS (e, fr, cur, nm, nl, next, l.gap)
+  const StepLaunch l = step_launch<S>(e, nm + nl + (next.pose ? skin_items<BT>(e.n) : 0), bulk, 5 * 1024);
+#define LBM_STEP_ARGS (e, fr, cur, nm, nl, next)
   LBM_STEP_FORM(k_step_macro, l.grid, BT, l.lds, s);
 #undef LBM_STEP_ARGS
 }
@@ -454,8 +451,8 @@ void step_interp_kernels(const EnvView &e, const FrameF &fr, int cur, bool rot, 
                          int first_bulk, int bulk, hipStream_t s) {
   const int front = nl > 0 ? (e.n + kStepMk - 1) / kStepMk + nl + (next.pose ? skin_items<BT>(e.n) : 0)
                            : interp_items<BT>(e.n);
-  const StepLaunch l = step_launch<S>(e, front, first_bulk, bulk, 5 * 1024);
-#define LBM_STEP_ARGS (e, fr, cur, nl, partials, next, l.first_bulk, l.gap)
+  const StepLaunch l = step_launch<S>(e, front, bulk, 5 * 1024);
+#define LBM_STEP_ARGS (e, fr, cur, nl, partials, next, first_bulk)
   LBM_STEP_FORM(k_step_interp, l.grid, BT, l.lds, s);
 #undef LBM_STEP_ARGS
 }
@@ -464,9 +461,9 @@ template <class S, bool TRT>
 void step_band_kernels(const EnvView &e, const FrameF &fr, int cur, bool rot, int force, float *wrench, int by_marker,
                        NextStep next, int first_bulk, hipStream_t s) {
   const int nt = std::min(8 * e.cap, kBandWorkgroups);
-  const StepLaunch l = step_launch<S>(e, nt + (wrench ? 1 : 0) + (next.pose ? active_items<BT>(e) : 0), first_bulk,
+  const StepLaunch l = step_launch<S>(e, nt + (wrench ? 1 : 0) + (next.pose ? active_items<BT>(e) : 0),
                                       bulk_blocks(e) - first_bulk, sizeof(SpreadLds<3>) + 4 * 1024);
-#define LBM_STEP_ARGS (e, fr, cur, nt, force, wrench, by_marker, next, l.first_bulk, l.gap)
+#define LBM_STEP_ARGS (e, fr, cur, nt, force, wrench, by_marker, next, first_bulk)
   LBM_STEP_FORM(k_step_band, l.grid, BT, l.lds, s);
 #undef LBM_STEP_ARGS
 }

@@ -48,19 +48,12 @@ struct NextStep {
   const float *pose;
 };
 
-// LDS a launch reserves beyond its own so that three 256-cell blocks of the F32
-// collide share a compute unit (see collide_lds), and the spacing of its marker
-// workgroups, both by how much bulk there is:
-//   F32 lattices of a million cells and more take the reservation (fish 547
-//   against 566 us; 192x96x96 115.6 against 117.1, the 128x64x64 fin 36.6
-//   against 36.0 us without); 2-byte ones never (fish 338 against 291 us);
-//   where the bulk of the launch is over eight times what the chip then holds,
-//   marker workgroups come eight (one per XCD) after every kGap bulk blocks, so
-//   that they never hold most of the few slots (fish 526 against 535 us); where
-//   it is less they come first, since the launch may end on them (192x96x96
-//   115.6 us first, 119.9 spaced; two fish 54.0, 55.9).
-constexpr int kGap = 56;
-constexpr int kCapBlocks = 4096, kCapResident = 768;  // blocks of BT cells; three on each of 256 compute units
+// F32 lattices of so many blocks of BT cells and more reserve LDS beyond a
+// launch's own so that three blocks of the collide share a compute unit (see
+// collide_lds): fish 547 against 566 us, 192x96x96 115.6 against 117.1, the
+// 128x64x64 fin 36.6 against 36.0 us without; 2-byte ones never (fish 338
+// against 291 us).
+constexpr int kCapBlocks = 4096;
 
 // Cell blk * BT + tid of the bulk, in x-fastest order. The tile map is read
 // beside the populations, not before them (the memory clobber keeps the pulls
@@ -145,20 +138,19 @@ __device__ inline void band_item(const EnvView &e, const BodySet &bs, const Fram
   __syncthreads();  // s is reused by the next item
 }
 
-// Which work workgroup blk of a launch has: nfront workgroups of marker work in
-// groups of eight (one per XCD), each group followed by `gap` bulk blocks, then
-// the rest of the bulk. Returns the marker workgroup (blk set to it) or false
-// (blk set to the bulk block). The grid is 8 ceil(nfront / 8) + bulk blocks, and
-// marker workgroups nfront and beyond have none.
-__device__ inline bool marker_block(int &blk, int nfront, int gap) {
-  const int groups = (nfront + 7) >> 3, per = 8 + gap, span = groups * per;
-  if (blk >= span) {
-    blk -= 8 * groups;
-    return false;
-  }
-  const int q = blk / per, r = blk - q * per;
-  blk = r < 8 ? 8 * q + r : gap * q + r - 8;
-  return r < 8;
+// Which work workgroup blk of a launch has: first nfront workgroups of marker
+// work (up to a multiple of eight, one per XCD, of which those past nfront have
+// none), then the bulk. Returns whether it is a marker workgroup, else blk is set
+// to the bulk block. Marker workgroups come first because the launch may end on
+// them: spread over it, those of a body with many active tiles started late (eight
+// after every 56 bulk blocks, sphere of radius 60 and 40,000 markers in
+// 384x192x192: 870 against 655 us a step, of radius 35 in 320x176x170 438 against
+// 391, 192x96x96 119.9 against 115.6; fish 526 against 528).
+__device__ inline bool marker_block(int &blk, int nfront) {
+  const int front = (nfront + 7) & ~7;
+  if (blk < front) return true;
+  blk -= front;
+  return false;
 }
 
 constexpr int kStepMk = BT / 64;  // markers per workgroup of k_step_interp, one wave each
@@ -167,12 +159,11 @@ constexpr int kStepMk = BT / 64;  // markers per workgroup of k_step_interp, one
 // lists (over the active tiles), skin_items for the next step (none without
 // one). The bulk starts at block 0.
 template <class S, bool XPER, bool ROT, bool YZ, bool TRT>
-__global__ void __launch_bounds__(BT, 4) k_step_macro(EnvView e, FrameF fr, int cur, int nm, int nl, NextStep next,
-                                                      int gap) {
+__global__ void __launch_bounds__(BT, 4) k_step_macro(EnvView e, FrameF fr, int cur, int nm, int nl, NextStep next) {
   const int tid = threadIdx.x;
   int blk = blockIdx.x;
   const int ns = next.pose != nullptr ? skin_items<BT>(e.n) : 0;
-  if (!marker_block(blk, nm + nl + ns, gap)) {
+  if (!marker_block(blk, nm + nl + ns)) {
     bulk_cell<S, XPER, ROT, YZ, TRT>(e, e.b[0], fr, cur, blk, tid);
   } else if (blk < nm) {
     const XcdWalk w = xcd_walk(2 * n_active_of(e, e.b[0]), blk, nm);
@@ -191,12 +182,12 @@ __global__ void __launch_bounds__(BT, 4) k_step_macro(EnvView e, FrameF fr, int 
 // starts at block first_bulk.
 template <class S, bool XPER, bool ROT, bool YZ, bool TRT>
 __global__ void __launch_bounds__(BT, 4) k_step_interp(EnvView e, FrameF fr, int cur, int nl, float *partials,
-                                                       NextStep next, int first_bulk, int gap) {
+                                                       NextStep next, int first_bulk) {
   const int tid = threadIdx.x;
   int blk = blockIdx.x;
   const int ni = nl > 0 ? (e.n + kStepMk - 1) / kStepMk : interp_items<BT>(e.n);
   const int ns = nl > 0 && next.pose != nullptr ? skin_items<BT>(e.n) : 0;
-  if (!marker_block(blk, ni + nl + ns, gap)) {
+  if (!marker_block(blk, ni + nl + ns)) {
     bulk_cell<S, XPER, ROT, YZ, TRT>(e, e.b[0], fr, cur, first_bulk + blk, tid);
   } else if (blk < ni) {
     if (nl > 0) {
@@ -219,11 +210,11 @@ __global__ void __launch_bounds__(BT, 4) k_step_interp(EnvView e, FrameF fr, int
 // The bulk starts at block first_bulk.
 template <class S, bool XPER, bool ROT, bool YZ, bool TRT>
 __global__ void __launch_bounds__(BT, 4) k_step_band(EnvView e, FrameF fr, int cur, int nt, int force, float *wrench,
-                                                     int by_marker, NextStep next, int first_bulk, int gap) {
+                                                     int by_marker, NextStep next, int first_bulk) {
   const int tid = threadIdx.x;
   int blk = blockIdx.x;
   const int nw = wrench != nullptr ? 1 : 0, nb = next.pose != nullptr ? active_items<BT>(e) : 0;
-  if (!marker_block(blk, nt + nw + nb, gap)) {
+  if (!marker_block(blk, nt + nw + nb)) {
     bulk_cell<S, XPER, ROT, YZ, TRT>(e, e.b[0], fr, cur, first_bulk + blk, tid);
   } else if (blk < nt) {
     __shared__ SpreadLds<3> s;
