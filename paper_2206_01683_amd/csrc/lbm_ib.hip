@@ -600,7 +600,7 @@ lbm_status step_beside_t(lbm_ctx *c, const lbm_markers *m, const float *poses, c
   const size_t pose_stride = (size_t)m->nbones * 24;
   const bool one_pass = c->p.ib_scheme == LBM_IB_DIRECT && c->p.mdf_iters == 1;
   const bool macros = !one_pass || e.n > kDirectMarkers;
-  const int nl = std::min(c->L.cap, kListWorkgroups);
+  const int nl = list_workgroups(e);
   const int share = (int)((int64_t)bulk_blocks(e) * kBulkShare / 16);
   lbm_status st;
   prof_mark(c, 0);
@@ -1133,7 +1133,7 @@ lbm_status segment_record(lbm_ctx *c, const void *ckpt, void *const *ring, int32
         body_at_slot(e.b[1], rs, rbase + rs.total * (size_t)(t + 1));
         next.pose = poses + pstride * (t + 1);
       }
-      const int nl = std::min(c->L.cap, kListWorkgroups);
+      const int nl = list_workgroups(e);
       const int share = (int)((int64_t)bulk_blocks(e) * kBulkShare / 16);
       step_macro_kernels<StoreF32, false>(e, fr, 0, false, nl, next, share, c->stream);
       step_interp_kernels<StoreF32, false>(e, fr, 0, false, 0, wr ? e.partials : nullptr, next, share, share, c->stream);

@@ -40,8 +40,19 @@ constexpr int kDirectMarkers = 2000;
 // marker work there (2, 3 and 4 of them: fin 37.3, 37.2, 36.0 us, fish 539,
 // 537, 535 us).
 constexpr int kBulkShare = 4;
-// Most marker workgroups over tile parts, marker lists and planes.
-constexpr int kMacroWorkgroups = 1024, kListWorkgroups = 256, kBandWorkgroups = 1024;
+// Most marker workgroups over tile parts and planes (steps of the fish and of
+// spheres of 9,000 to 40,000 markers with 2,048 of either: the same within 1.2%;
+// with 4,096 for the planes up to 4% longer).
+constexpr int kMacroWorkgroups = 1024, kBandWorkgroups = 1024;
+// Marker workgroups over the marker lists: one for 64 markers, at least 256. A
+// list takes as long as there are chunks of markers to look through and markers in
+// the tile, so many markers want a workgroup for every tile (192x96x96 in steps of
+// the sphere of radius 30, 256 of them against this: 50,000 markers 150, 137 us,
+// 200,000 431, 326, 1,000,000 1,895, 1,376; twice as many the same within 1%).
+inline int list_workgroups(const EnvView &e) {
+  const int most = e.n / 64 > 256 ? e.n / 64 : 256;
+  return e.cap < most ? e.cap : most;
+}
 
 // The next step's skinning and binning, beside this step (pose null: none).
 struct NextStep {
