@@ -1529,9 +1529,17 @@ BatchArgs batch_args(const lbm_batch *b) {
   return a;
 }
 
+// The F32 kinds reserve LDS as the single lattice's collide does, so that few
+// waves share a compute unit also where another batch's launches run beside this
+// one's: its collides otherwise fill what waves are left and slow each other (three
+// batches in turn on streams of their own, us a step of one without and with it,
+// and with kMacroGroups: 4 lattices 143.1, 139.9, 138.0; 14 453.9, 448.3, 447.7; 36
+// 1,088.8, 1,075.5, 1,079.5; one batch alone the same within 1%). The 2-byte kinds
+// don't (30 lattices, FP16: 574 us alone, 674 with it).
 template <int K>
 void launch_kb_collide(const BatchArgs &a, int s, int item0, int n, hipStream_t st) {
-  kb_collide<K><<<n, WG, 0, st>>>(a, a.envs, a.pre, a.corder, s, item0);
+  const size_t lds = collide_lds<typename StoreOf<(K >> 4)>::type>(dim3(WG));
+  kb_collide<K><<<n, WG, lds, st>>>(a, a.envs, a.pre, a.corder, s, item0);
 }
 
 template <int... K>
@@ -1570,6 +1578,9 @@ lbm_status batch_enqueue_t(lbm_batch *b, int nsteps, int mode) {
   }
   const int gdyn = (int)std::max<int64_t>(
       8, std::min<int64_t>(4 * cap_items, std::max<int64_t>(1024, std::min<int64_t>(markers / 32, 4096))));
+  // The band macros' workgroups, of 512 threads, do well with two on each compute
+  // unit (see launch_kb_collide; 48 lattices 1,516 us a step, 1,514 with 512).
+  constexpr int kMacroGroups = 512;
   int nskin = 0, nbin = 0;  // workgroups for the next step
   // interpolation branches per environment only on rotation
   auto interp = [&](int s, int pass) {
@@ -1585,7 +1596,7 @@ lbm_status batch_enqueue_t(lbm_batch *b, int nsteps, int mode) {
   for (int s = 0; s < nsteps; ++s, a.set ^= 1) {
     nskin = s + 1 < nsteps ? b->tot[PRE_SKIN] : 0;
     nbin = s + 1 < nsteps ? b->tot[PRE_ACTIVE] : 0;
-    kb_macro<UNI><<<gdyn, WG, 0, b->stream>>>(a, s);
+    kb_macro<UNI><<<std::min(gdyn, kMacroGroups), WG, 0, b->stream>>>(a, s);
     if (b->implicit) {  // mdf = conjugate-gradient steps
       interp(s, 0);
       kb_cg_init<<<b->tot_cg, kCgWG, 0, b->stream>>>(a, s);
