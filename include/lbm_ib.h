@@ -157,7 +157,8 @@ typedef struct {
   int32_t block_x, block_y;  /* collide block: block_x (a multiple of 64) by block_y cells, or block_x
                                 consecutive cells of the x-fastest order when block_y = -1;
                                 0, 0 = default (256 consecutive cells with LBM_LAYOUT_ROWS,
-                                else 512). The shape of the collide's own launch (no body,
+                                else 128 x 4 or 64 x 8 where the width is a multiple of
+                                128, or of 64 below that, else 512). The shape of the collide's own launch (no body,
                                 ib_workgroups = -1, batches, the adjoint); beside the
                                 immersed-boundary phases blocks are 256 consecutive cells */
   int32_t with_adjoint;      /* nonzero: workspace also holds the adjoint buffers */
