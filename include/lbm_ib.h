@@ -234,15 +234,15 @@ lbm_status lbm_init(lbm_ctx **out, const lbm_params *p, void *f_a, void *f_b, vo
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): lbm_init
- * without a caller workspace. The context's workspace is a fixed array of
- * LBM_STATIC_WORKSPACE_BYTES (64 MiB) that the library holds on each device
- * it runs on until the process ends; the context itself is a per-device slot
+ * without a caller workspace. The context's workspace is a fixed array that
+ * the library holds on each device it runs on until the process ends (152 MiB:
+ * room for what LBM_STATIC_WORKSPACE_BYTES, 64 MiB, admits and for the second
+ * body set and marker lists beside it); the context itself is a per-device slot
  * of the library, so this call allocates no memory of any kind. Arguments as
  * lbm_init (f_a, f_b, rho0, u0, hip_stream) on the current device.
  * Errors: LBM_ERR_CAPACITY if what the tiles, the markers and the options ask
- * for (lbm_workspace_bytes(p) less the second body set, marker lists and wrench
- * shares, for which the library holds room beside it) exceeds
- * LBM_STATIC_WORKSPACE_BYTES (lower max_markers or max_active_tiles);
+ * for (lbm_workspace_bytes(p) less the second body set and the marker lists)
+ * exceeds LBM_STATIC_WORKSPACE_BYTES (lower max_markers or max_active_tiles);
  * LBM_ERR_ARG as lbm_init; LBM_ERR_DEVICE if the runtime cannot resolve the
  * array on this device.
  * Sharing: every context created this way on one device is the same slot and

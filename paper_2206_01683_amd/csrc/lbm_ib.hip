@@ -153,9 +153,8 @@ Layout layout(const lbm_params *p) {
 }
 
 // Workspace bytes that count against LBM_STATIC_WORKSPACE_BYTES: tiles, markers
-// and what the options ask for, without the second body set, the marker
-// lists and the markers' wrench shares (whose room the static array has beside
-// that limit).
+// and what the options ask for, without the second body set and the marker lists
+// (whose room the static array has beside that limit).
 size_t static_need(const lbm_params *p) {
   const Layout L = layout(p);
   const size_t m = L.maxm, nt = L.ntiles, cap = L.cap;
@@ -758,11 +757,11 @@ lbm_status setup_ctx(lbm_ctx *c, const lbm_params *p, void *f_a, void *f_b, char
 // shared by every such context on that device. Host code reaches it only
 // through the address hipGetSymbolAddress returns for the current device;
 // the array's name in host code is not a device address.
-// What lbm_init_static admits (static_need) leaves out the second body set, the
-// marker lists and the markers' wrench shares: at most 28 bytes an active tile
-// and 77 + 4 * 27 a marker, which the array holds on top (a problem at the
-// limit has at most 3,200 active tiles or 0.64M markers).
-constexpr size_t kStaticWorkspaceBytes = LBM_STATIC_WORKSPACE_BYTES + ((size_t)116 << 20);
+// What lbm_init_static admits (static_need) leaves out the second body set and the
+// marker lists: at most 28 bytes an active tile and 46 + 4 * 27 a marker, which the
+// array holds on top (a problem at the limit has at most 3,200 active tiles or
+// 0.64M markers, 0.57M with slip walls; 86 MiB).
+constexpr size_t kStaticWorkspaceBytes = LBM_STATIC_WORKSPACE_BYTES + ((size_t)88 << 20);
 constexpr int kMaxStaticDevices = 64;
 __device__ __align__(256) char scratch[kStaticWorkspaceBytes];
 
@@ -827,7 +826,7 @@ lbm_status lbm_init_static(lbm_ctx **out, const lbm_params *p, void *f_a, void *
                            const float *u0, void *hip_stream) {
   if (!out || !params_ok(p) || !f_a || !f_b || f_a == f_b) return LBM_ERR_ARG;
   *out = nullptr;
-  if (static_need(p) > LBM_STATIC_WORKSPACE_BYTES) return LBM_ERR_CAPACITY;
+  if (static_need(p) > LBM_STATIC_WORKSPACE_BYTES || layout(p).total > kStaticWorkspaceBytes) return LBM_ERR_CAPACITY;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return LBM_ERR_DEVICE;
   if (dev < 0 || dev >= kMaxStaticDevices) return LBM_ERR_UNSUPPORTED;
