@@ -470,12 +470,15 @@ lbm_status lbm_body_forces(lbm_ctx *c, const lbm_markers *m, const double *cente
  * range), or LBM_OK. Clears the guards. */
 lbm_status lbm_check(lbm_ctx *c);
 
-/* Measurement hook. enable != 0: every later step brackets its two phases
- * (immersed-boundary kernels; fused collide-stream kernel) with HIP events on
- * the context stream (event pool of 4096 steps; later steps are not timed).
- * lbm_profile_collect synchronizes, returns the summed durations in
- * milliseconds and the number of timed steps, and empties the pool. Either
- * output may be NULL. */
+/* Measurement hook. enable != 0: every later step of lbm_ib_step is timed with
+ * HIP events on the context stream (event pool of 4096 steps; later steps are not
+ * timed). lbm_profile_collect synchronizes, returns the summed durations in
+ * milliseconds of two parts and the number of timed steps, and empties the pool.
+ * With every phase in a launch of its own (ib_workgroups = -1, or no body) the
+ * parts are the immersed-boundary kernels and the collides. Beside the collide the
+ * phases have no time of their own: *ib_ms is then what runs before a call's first
+ * step (its skinning and binning) and *collide_ms the steps, phases included.
+ * Either output may be NULL. */
 lbm_status lbm_profile_enable(lbm_ctx *c, int enable);
 lbm_status lbm_profile_collect(lbm_ctx *c, double *ib_ms, double *collide_ms, int64_t *steps);
 

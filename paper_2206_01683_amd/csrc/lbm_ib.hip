@@ -189,9 +189,10 @@ struct lbm_ctx {
   bool slots_dirty;
   bool is_static;  // created by lbm_init_static: workspace in `scratch`, not freed by lbm_destroy
   int bx, by;
-  // measurement hook: up to 3 events per timed step (start, after IB, after
-  // collide); prof_chained[s]: step s of a one-launch run records only its
-  // end, and starts at the previous step's end (no IB before its launch)
+  // measurement hook: up to 3 events per timed step (start, the step's first
+  // launch that collides, end); prof_chained[s]: step s follows another of the same
+  // call beside whose collide its markers were skinned and binned, records only its
+  // end, and starts at the previous step's end
   bool prof;
   std::vector<hipEvent_t> ev;
   std::vector<unsigned char> prof_chained;

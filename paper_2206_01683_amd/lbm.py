@@ -331,7 +331,10 @@ class Simulation:
         _check(lib().lbm_profile_enable(self.ctx, 1 if enable else 0), "lbm_profile_enable")
 
     def profile_collect(self):
-        """(ib_ms_total, collide_ms_total, timed_steps) since the last collect."""
+        """(ib_ms_total, collide_ms_total, timed_steps) since the last collect.
+        With ib_workgroups = -1 or without a body the immersed-boundary kernels
+        and the collides; otherwise what runs before each call's first step, and
+        the steps, whose phases run beside the collide."""
         a, b, n = ctypes.c_double(), ctypes.c_double(), ctypes.c_int64()
         _check(lib().lbm_profile_collect(self.ctx, ctypes.byref(a), ctypes.byref(b), ctypes.byref(n)),
                "lbm_profile_collect")
