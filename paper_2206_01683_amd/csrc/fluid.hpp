@@ -371,13 +371,24 @@ __global__ void k_init_equilibrium(const float *__restrict__ rho0, const float *
   }
 }
 
-// Zeroes the elements of a population buffer that hold no population, so that
-// a buffer can be read as a whole. One workgroup per plane of the buffer.
-template <class S>
-__global__ void k_clear_padding(typename S::T *__restrict__ buf, GridArgs g) {
-  const size_t n = (size_t)g.nx * g.ny * g.nz, pad = g.plane - n, i = blockIdx.x;
-  const size_t at = g.ps == g.plane ? i * g.plane + n : Q * n + i * pad;  // planes : rows
-  for (size_t q = threadIdx.x; q < pad; q += blockDim.x) buf[at + q] = typename S::T(0);
+// What a new context needs cleared, in one launch: the tile flags, both tile maps
+// (no tile active), guard and counters, and the elements of both population buffers
+// that hold no population, so that a buffer can be read as a whole (one element is
+// `units` 2-byte words; all of them zero is 0 in every format).
+__global__ void __launch_bounds__(256) k_clear_start(EnvView e, int units) {
+  const int t0 = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+  for (int t = t0; t < e.ntiles; t += nt) {
+    e.tile_flag[t] = 0;
+    e.b[0].tile_slot[t] = e.b[1].tile_slot[t] = -1;
+  }
+  if (t0 < 16) e.guard[t0] = e.b[0].counters[t0] = e.b[1].counters[t0] = 0;
+  const GridArgs &g = e.g;
+  const size_t n = (size_t)g.nx * g.ny * g.nz, pad = g.plane - n, per = pad * units;
+  for (size_t q = t0; q < Q * per; q += nt) {
+    // planes: the end of each; rows: the end of the buffer
+    const size_t i = q / per, at = (g.ps == g.plane ? (i * g.plane + n) * units + q % per : Q * n * units + q);
+    for (int b = 0; b < 2; ++b) ((uint16_t *)e.f[b])[at] = 0;
+  }
 }
 
 // Stored buffer -> canonical pre-collision populations (pull with wrap/clamp).

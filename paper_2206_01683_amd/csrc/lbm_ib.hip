@@ -656,8 +656,6 @@ template <class S>
 lbm_status init_eq(lbm_ctx *c, const float *rho0, const float *u0) {
   GridArgs g = grid_args(c);
   dim3 grid((c->p.nx + 63) / 64, c->p.ny, c->p.nz);
-  for (int q = 0; q < 2; ++q)
-    k_clear_padding<S><<<Q, 256, 0, c->stream>>>(static_cast<typename S::T *>(c->f[q]), g);
   k_init_equilibrium<S><<<grid, 64, 0, c->stream>>>(rho0, u0, static_cast<typename S::T *>(c->f[c->cur]), g);
   return launched();
 }
@@ -740,15 +738,10 @@ lbm_status setup_ctx(lbm_ctx *c, const lbm_params *p, void *f_a, void *f_b, char
   }
   c->bx = bx;
   c->by = by;
-  // every workspace field that must start cleared, by kernels (no memset
-  // nodes, so the sequence can sit in a captured graph)
-  k_fill_int<<<256, 256, 0, c->stream>>>(wsp<int>(c, c->L.tile_flag), 0, c->L.ntiles);
-  k_fill_int<<<1, 64, 0, c->stream>>>(wsp<int>(c, c->L.guard), 0, 16);
-  for (int q = 0; q < 2; ++q) {
-    k_fill_int<<<256, 256, 0, c->stream>>>(wsp<int>(c, c->L.tile_slot[q]), -1, c->L.ntiles);
-    k_fill_int<<<1, 64, 0, c->stream>>>(wsp<int>(c, c->L.counters[q]), 0, 16);
-  }
-  lbm_status st = launched();
+  // everything that must start cleared, by a kernel (no memset nodes, so the
+  // sequence can sit in a captured graph)
+  k_clear_start<<<64, 256, 0, c->stream>>>(env_view(c, nullptr), (int)elem_bytes(p->storage) / 2);
+  const lbm_status st = launched();
   if (st != LBM_OK) return st;
   return LBM_BY_STORAGE(c, init_eq, rho0, u0);
 }
