@@ -36,7 +36,8 @@ HBM_PEAK_GBS = 8000.0
 BYTES_PER_CELL = {"f32": 216, "f16": 108, "bf16": 108}
 METRIC = "MLUPS and % of HBM roofline per GPU; adjoint/forward time ratio"
 # lbm_params.ib_workgroups of the headline: 0 and more run the immersed-boundary
-# phases beside the collide (k_step), -1 in launches of their own (k_collide).
+# phases beside the collide (k_step), all values alike; -1 in launches of their
+# own (k_collide).
 HEADLINE_IB_WORKGROUPS = 32
 _CSRC = os.path.join(ROOT, "paper_2206_01683_amd", "csrc")
 # the sources each main kernel is compiled from, and its committed HBM traffic summary

@@ -4,18 +4,18 @@
 // The immersed force lives only in "active" 8x8x8 tiles: tiles that some
 // marker's 4x4x4 Peskin stencil touches. Each step rebuilds the active set.
 // Every phase is a device function of (environment, work item) run by one
-// workgroup, so the same code serves the single-lattice kernels, the batched
+// workgroup of NT threads (256 in the single lattice's launches, mostly 512 in the
+// batched ones), so the same code serves the single-lattice kernels, the batched
 // per-phase kernels and the persistent batched kernel:
-//   skin_item     512 markers: linear blend skinning, wrap/range guard, flag
+//   skin_item     NT markers: linear blend skinning, wrap/range guard, flag
 //                 the tiles each stencil touches (plain stores), per-wave
 //                 chunk boxes (tile range of 64 consecutive markers)
-//   active_item   512 tiles: compact the flags into slots and an active list
+//   active_item   NT tiles: compact the flags into slots and an active list
 //   list_item     one active tile: the list of the markers that touch it
-//   macro_item    one active tile: density and unforced velocity of its 512
-//                 cells
+//   macro_item    NT cells of an active tile: density and unforced velocity
 //   interp_item,  U*_k, rho_k, direct forcing F_k, marker record, wrench
 //   interp_wave   shares; from the band macros, or straight from the populations
-//   spread_planes one z-plane of an active tile per 256 threads: its markers add
+//   spread_plane  one z-plane of an active tile per 256 threads: its markers add
 //                 their stencil nodes into LDS in 64-bit fixed point
 //                 (order-independent, so deterministic)
 //   wrench_sum    adds the wrench partials in a fixed order
@@ -27,7 +27,7 @@
 
 namespace lbmib {
 
-constexpr int WG = 512;              // threads per workgroup in every IB phase
+constexpr int WG = 512;              // threads per workgroup of the batched phases, k_active, k_macro and the adjoint
 constexpr int REC = 20;              // floats per marker record: w[12], base[3], pad, fdv[3], pad
 constexpr int kWavePer = WG / 64;    // markers per item of the one-wave-per-marker kernels (adjoint)
 constexpr int kInterpMk = WG / 16;   // markers per CG apply item, 16 lanes each

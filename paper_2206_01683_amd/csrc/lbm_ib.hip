@@ -397,9 +397,12 @@ lbm_status launch_collide(lbm_ctx *c, const EnvView &e, const FrameF &fr, bool r
 
 // The marker phases beside the collide (step.hpp) unless ib_workgroups = -1 asks
 // for every phase in a launch of its own before it. Steps in launches of their
-// own against beside: 64x32x32 sphere 36.4, 15.8 us; 128x64x64 fin 57.4, 36.0;
-// 150x50x100 two fish 93.1 (54 with linear collide blocks), 54.0; 384x192x192
-// fish 570, 526, in FP16 300, 291.
+// own against beside, us: 64x32x32 sphere 35.6, 16.9; 128x64x64 fin 55.9, 36.4;
+// 150x50x100 fish of 4,000 markers 74.2, 57.1; 384x192x192 fish 545, 530, in FP16
+// 297, 282. Bodies whose band is a few percent of a large lattice, which the host
+// doesn't know, do better in launches of their own: sphere of radius 35 in
+// 320x176x170 392, 389, of radius 40 in 384x192x192 569, 578, of radius 60 606, 657,
+// in FP16 353, 379.
 bool beside_collide(const lbm_ctx *c) { return c->p.ib_workgroups >= 0; }
 
 // Launches the form of KERNEL for (S, e, rot, TRT) with LBM_STEP_ARGS.
@@ -1561,9 +1564,8 @@ lbm_status batch_enqueue_t(lbm_batch *b, int nsteps, int mode) {
     return launched();
   }
   // Workgroups over the active tiles, whose number only the device knows: one for
-  // 32 markers, between 1,024 and 4,096. Each scans
-  // the environments' counts first, which workgroups without a tile do for
-  // nothing (16 bf16 lattices in groups of 32,000 markers: 352 us a step with
+  // 32 markers, between 1,024 and 4,096. Each scans the environments' counts
+  // first, which workgroups without a tile do for nothing (16 bf16 lattices in groups of 32,000 markers: 352 us a step with
   // 1,024, 356 with 2,048, 365 with 4,096; 48 lattices, 194,000: 1,612, 1,610,
   // 1,594).
   int64_t cap_items = 0, markers = 0;
