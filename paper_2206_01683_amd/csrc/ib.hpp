@@ -790,10 +790,10 @@ __device__ inline void wrench_sum(const float *__restrict__ partials, int n, boo
 
 // --------------------------------------------------------------- spreading --
 // The immersed force of one z-plane (64 cells) of an active tile per 256
-// threads: g(x) = sum_k F_k dV_k delta(x - X_k). The plane's markers are those
-// entries of the tile's list whose stencil has a node at this z; their records
-// are staged in LDS, kStage at a time, and taken by four lanes each, one lane
-// per x-row of the stencil in this plane, which adds the row's nodes inside the
+// threads: g(x) = sum_k F_k dV_k delta(x - X_k). The plane's markers, those
+// entries of the tile's list whose stencil has a node at this z, are collected in
+// LDS, up to kHits of the list at a time; four lanes each take one, one lane per
+// x-row of the stencil in this plane, which adds the row's nodes inside the
 // tile into the plane's LDS cells with 64-bit LDS atomics (2^-40 fixed point).
 // Integer sums make the result independent of every order, and a plane belongs
 // to one workgroup, so its force is stored, or used from LDS, without global
@@ -801,15 +801,25 @@ __device__ inline void wrench_sum(const float *__restrict__ partials, int n, boo
 // Planes, not tiles: the markers of a thin body crowd into few tiles (the
 // 128x64x64 fin has 32 active ones, with up to 579 of its 3,000 markers), and
 // the conversion to fixed point and the LDS atomics of one crowded tile on one
-// compute unit were the whole phase's time.
-constexpr int kStage = 256;  // marker records of a plane in LDS at a time
+// compute unit were the whole phase's time. The records are read where they are
+// used, U markers in flight in each group of four lanes: staged in LDS, 256 at a
+// time, each stage was a chain of a load and three barriers that crowded tiles
+// went through many times.
+constexpr int kHits = 1024;
+
+// w[q] becomes w[(q + r) & 3].
+__device__ inline void rotate4(float (&w)[4], int r) {
+  const float a0 = r & 1 ? w[1] : w[0], a1 = r & 1 ? w[2] : w[1], a2 = r & 1 ? w[3] : w[2], a3 = r & 1 ? w[0] : w[3];
+  w[0] = r & 2 ? a2 : a0;
+  w[1] = r & 2 ? a3 : a1;
+  w[2] = r & 2 ? a0 : a2;
+  w[3] = r & 2 ? a1 : a3;
+}
 
 template <int NC>
 struct alignas(16) SpreadLds {
-  unsigned long long acc[NC][64];
-  float wx[kStage][4], wy[kStage][4], v[kStage][NC];  // v: the spread values
-  float wz[kStage];
-  int bx[kStage], by[kStage];
+  unsigned long long acc[2 * NC][64];  // the plane's cells; the second half takes the nodes outside, and is not read
+  int hit[kHits];  // k | node << kListShift: the marker and its stencil node at this z
   int nhit;
 };
 
@@ -821,72 +831,73 @@ __device__ inline void cg_direction(const EnvView &e, int k, const float *beta, 
 // the implicit correction's conjugate-gradient step (cg_direction with beta,
 // first). s.acc holds the start value (visible after the first barrier here);
 // a barrier ends the call.
-template <bool CG, int NC = 3, int FIRST = 16>
+template <bool CG, int NC = 3, int FIRST = 16, int U = 2>
 __device__ inline void spread_plane(const EnvView &e, const BodySet &bs, const TileAt &t, int plane, int tid,
                                     SpreadLds<NC> &s, const float *beta = nullptr, bool first = true) {
   const GridArgs &g = e.g;
   const int x0 = t.x * 8, y0 = t.y * 8, lane = tid & 63;
   const int n = e.n;
   const gmem<int> *list = (const gmem<int> *)e.list + t.off;
-  int entry = tid < t.cnt ? list[tid] : 0;
-  for (int c0 = 0; c0 < t.cnt; c0 += kStage) {
+  constexpr int PER = kHits / 256, kMask = (1 << kListShift) - 1;
+  for (int c0 = 0; c0 < t.cnt; c0 += kHits) {
+    int entry[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) entry[r] = c0 + 256 * r + tid < t.cnt ? list[c0 + 256 * r + tid] : 0;
     if (tid == 0) s.nhit = 0;
     __syncthreads();
-    const bool in = c0 + tid < t.cnt;
-    const int k = entry & ((1 << kListShift) - 1);
-    int sz = plane + 3 - (int)((unsigned)entry >> kListShift);  // the stencil node at this z, modulo nz
-    sz = sz < 0 ? sz + g.nz : (sz >= g.nz ? sz - g.nz : sz);
-    const bool hit = in && sz < 4;
-    if (c0 + kStage + tid < t.cnt) entry = list[c0 + kStage + tid];
-    const unsigned long long bal = __ballot(hit);
-    int at = 0;
-    if (lane == 0 && bal != 0ull) at = atomicAdd(&s.nhit, (int)__popcll(bal));
-    at = __builtin_amdgcn_readfirstlane(at) + __popcll(bal & ((1ull << lane) - 1ull));
-    if (hit) {
-      const gmem<vfloat4> *rp = (const gmem<vfloat4> *)e.rec + (size_t)k * (REC / 4);
-      const vfloat4 wx = rp[0], wy = rp[1], ba = rp[3], fd = rp[4];
-      const float wz = ((const gmem<float> *)rp)[8 + sz];
-      *(vfloat4 *)s.wx[at] = wx;
-      *(vfloat4 *)s.wy[at] = wy;
-      s.wz[at] = wz;
-      s.bx[at] = __float_as_int(ba.x);
-      s.by[at] = __float_as_int(ba.y);
-      float v[4] = {ba.w, fd.x, fd.y, fd.z};  // record values 15 .. 18
-      if (CG) {
-        cg_direction(e, k, beta, first, v + 1);
-        if (e.slip) {  // the search direction is a normal force p n
-          const float p0 = v[1];
-          v[1] = p0 * bs.Nrm[k];
-          v[2] = p0 * bs.Nrm[n + k];
-          v[3] = p0 * bs.Nrm[2 * (size_t)n + k];
-        }
-      }
 #pragma unroll
-      for (int c = 0; c < NC; ++c) s.v[at][c] = v[FIRST - 15 + c];
+    for (int r = 0; r < PER; ++r) {
+      if (c0 + 256 * r >= t.cnt) break;  // uniform
+      int sz = plane + 3 - (int)((unsigned)entry[r] >> kListShift);  // the stencil node at this z, modulo nz
+      sz = sz < 0 ? sz + g.nz : (sz >= g.nz ? sz - g.nz : sz);
+      const bool hit = c0 + 256 * r + tid < t.cnt && sz < 4;
+      wave_push(hit, (int)((unsigned)(entry[r] & kMask) | (unsigned)sz << kListShift), s.hit, &s.nhit, kHits, lane);
     }
     __syncthreads();
     const int m = s.nhit;
-    for (int j = tid >> 2; j < m; j += 64) {
-      const int ly = wrap_idx(s.by[j] + (lane & 3), g.ny) - y0;
-      if ((unsigned)ly >= 8u) continue;
-      const int bx = s.bx[j];
-      const float wyz = s.wy[j][lane & 3] * s.wz[j];
-      float v[NC];
+    for (int j0 = tid >> 2; j0 < m; j0 += 64 * U) {
+      vfloat4 wx[U], ba[U], fd[U];  // the record: x weights, base and value 15, values 16 .. 18
+      float wyz[U];
 #pragma unroll
-      for (int c = 0; c < NC; ++c) v[c] = s.v[j][c];
+      for (int u = 0; u < U; ++u) {
+        const int h = s.hit[min(j0 + 64 * u, m - 1)], k = h & kMask;
+        const gmem<float> *rp = (const gmem<float> *)e.rec + (size_t)k * REC;
+        wx[u] = *(const gmem<vfloat4> *)rp;
+        ba[u] = *(const gmem<vfloat4> *)(rp + 12);
+        fd[u] = *(const gmem<vfloat4> *)(rp + 16);
+        wyz[u] = rp[4 + (lane & 3)] * rp[8 + (int)((unsigned)h >> kListShift)];
+        if (CG) {
+          float v[3];
+          cg_direction(e, k, beta, first, v);
+          if (e.slip) {  // the search direction is a normal force p n
+            const float p0 = v[0];
+            v[0] = p0 * bs.Nrm[k];
+            v[1] = p0 * bs.Nrm[n + k];
+            v[2] = p0 * bs.Nrm[2 * (size_t)n + k];
+          }
+          fd[u] = vfloat4{v[0], v[1], v[2], 0.f};
+        }
+      }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int u = 0; u < U; ++u) {
+        const int ly = wrap_idx(__float_as_int(ba[u].y) + (lane & 3), g.ny) - y0;
+        const bool row = j0 + 64 * u < m && (unsigned)ly < 8u;
         // neighbouring markers start at different nodes of their rows: a wave's
         // markers crowd on the same cells, and LDS atomics on one cell come one
         // after the other (48 lattices of 4,045 markers: 149 to 116 us with a
-        // wave a plane, 93 to 73 as here)
-        const int i = (q + (lane >> 2)) & 3;
-        const int lx = (g.xper ? wrap_idx(bx + i, g.nx) : bx + i) - x0;
-        if ((unsigned)lx >= 8u) continue;
-        const float d = s.wx[j][i] * wyz;
-        const int cell = lx | (ly << 3);
+        // wave a plane, 93 to 73 with 256 threads)
+        float w[4] = {wx[u].x, wx[u].y, wx[u].z, wx[u].w};
+        rotate4(w, lane >> 2);
+        const float v[4] = {ba[u].w, fd[u].x, fd[u].y, fd[u].z};  // record values 15 .. 18
 #pragma unroll
-        for (int c = 0; c < NC; ++c) atomicAdd(&s.acc[c][cell], to_fix(v[c] * d));
+        for (int q = 0; q < 4; ++q) {
+          const int bx = __float_as_int(ba[u].x) + ((q + (lane >> 2)) & 3);
+          const int lx = (g.xper ? wrap_idx(bx, g.nx) : bx) - x0;
+          const int cell = row && (unsigned)lx < 8u ? lx | (ly << 3) : 64 * NC + lane;
+          const float d = w[q] * wyz[u];
+#pragma unroll
+          for (int c = 0; c < NC; ++c) atomicAdd(&s.acc[0][0] + 64 * c + cell, to_fix(v[FIRST - 15 + c] * d));
+        }
       }
     }
     __syncthreads();
