@@ -353,8 +353,10 @@ __global__ void __launch_bounds__(WG) kb_skin(BatchArgs b) { phase_skin(b, 0, b.
 
 __global__ void __launch_bounds__(WG) kb_active(BatchArgs b) { phase_active(b, b.set, blockIdx.x, threadIdx.x); }
 
+// Six waves a SIMD, three workgroups a compute unit: left alone, the mixed form
+// takes one register too many for them.
 template <bool UNI>
-__global__ void __launch_bounds__(WG) kb_macro(BatchArgs b, int s) {
+__global__ void __launch_bounds__(WG, 6) kb_macro(BatchArgs b, int s) {
   __shared__ int s_pre[kMaxEnvs + 1];
   const XcdWalk w = xcd_walk(dynamic_prefix(b, 1, s_pre, threadIdx.x));
   for (int item = w.first; item < w.end; item += w.step) phase_macro<UNI, true>(b, s, item, s_pre, threadIdx.x);

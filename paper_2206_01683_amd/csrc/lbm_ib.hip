@@ -438,11 +438,13 @@ StepLaunch step_launch(const EnvView &e, int front, int bulk, size_t lds_own) {
   return {((front + 7) & ~7) + bulk, want > lds_own ? want - lds_own : 0};
 }
 
+constexpr size_t kListOwn = (kListLdsLone + BT) * sizeof(int);  // the marker lists' LDS
+
 template <class S, bool TRT>
 void step_macro_kernels(const EnvView &e, const FrameF &fr, int cur, bool rot, int nl, NextStep next, int bulk,
                         hipStream_t s) {
   const int nm = std::min(2 * e.cap, kMacroWorkgroups);
-  const StepLaunch l = step_launch<S>(e, nm + nl + (next.pose ? skin_items<BT>(e.n) : 0), bulk, 5 * 1024);
+  const StepLaunch l = step_launch<S>(e, nm + nl + (next.pose ? skin_items<BT>(e.n) : 0), bulk, kListOwn);
 #define LBM_STEP_ARGS (e, fr, cur, nm, nl, next)
   LBM_STEP_FORM(k_step_macro, l.grid, BT, l.lds, s);
 #undef LBM_STEP_ARGS
@@ -454,7 +456,7 @@ void step_interp_kernels(const EnvView &e, const FrameF &fr, int cur, bool rot, 
                          int first_bulk, int bulk, hipStream_t s) {
   const int front = nl > 0 ? (e.n + kStepMk - 1) / kStepMk + nl + (next.pose ? skin_items<BT>(e.n) : 0)
                            : interp_items<BT>(e.n);
-  const StepLaunch l = step_launch<S>(e, front, bulk, 5 * 1024);
+  const StepLaunch l = step_launch<S>(e, front, bulk, kListOwn);
 #define LBM_STEP_ARGS (e, fr, cur, nl, partials, next, first_bulk)
   LBM_STEP_FORM(k_step_interp, l.grid, BT, l.lds, s);
 #undef LBM_STEP_ARGS

@@ -182,7 +182,7 @@ __global__ void __launch_bounds__(BT, 4) k_step_macro(EnvView e, FrameF fr, int 
     for (int h = w.first; h < w.end; h += w.step) macro_item<BT, S, ROT>(e, e.b[0], fr, cur, h, tid);
   } else if (blk < nm + nl) {
     const int na = n_active_of(e, e.b[0]);
-    for (int slot = blk - nm; slot < na; slot += nl) list_item<BT>(e, e.b[0], slot, tid);
+    for (int slot = blk - nm; slot < na; slot += nl) list_item<BT, kListLdsLone, 8>(e, e.b[0], slot, tid);
   } else if (blk < nm + nl + ns) {
     skin_item<BT>(e, e.b[1], next.pose, blk - nm - nl, tid);
   }
@@ -210,7 +210,7 @@ __global__ void __launch_bounds__(BT, 4) k_step_interp(EnvView e, FrameF fr, int
     }
   } else if (blk < ni + nl) {
     const int na = n_active_of(e, e.b[0]);
-    for (int slot = blk - ni; slot < na; slot += nl) list_item<BT>(e, e.b[0], slot, tid);
+    for (int slot = blk - ni; slot < na; slot += nl) list_item<BT, kListLdsLone, 8>(e, e.b[0], slot, tid);
   } else if (blk < ni + nl + ns) {
     skin_item<BT>(e, e.b[1], next.pose, blk - ni - nl, tid);
   }
