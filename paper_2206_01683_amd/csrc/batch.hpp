@@ -23,8 +23,8 @@
 // cells of lattices this small, is read and written in 32-byte rows whose lines
 // a collide beside them drives out of L2 (48 lattices of 0.3 to 1.3 million
 // cells: macros 93 and band collides 282 us alone, 194 and 585 us more beside).
-// One step there takes 1,533 us: collide 1,337, band macros and lists 68,
-// spreading and binning 75, interpolation and skinning 53. Of two concurrent
+// One step there takes 1,516 us: collide 1,327, band macros and lists 68,
+// spreading and binning 61, interpolation and skinning 53. Of two concurrent
 // groups (16 bf16 lattices, 320 us a step) the collide of one holds the chip's wave
 // slots until it drains: of the time 47% is one collide alone, 18% both, 22% one
 // group's marker phases alone, 5% both groups', 5% a collide beside phases.

@@ -818,10 +818,12 @@ __device__ inline void wrench_sum(const float *__restrict__ partials, int n, boo
 // Planes, not tiles: the markers of a thin body crowd into few tiles (the
 // 128x64x64 fin has 32 active ones, with up to 579 of its 3,000 markers), and
 // the conversion to fixed point and the LDS atomics of one crowded tile on one
-// compute unit were the whole phase's time. The records are read where they are
-// used, U markers in flight in each group of four lanes: staged in LDS, 256 at a
-// time, each stage was a chain of a load and three barriers that crowded tiles
-// went through many times.
+// compute unit were the whole phase's time. Two markers in flight in each group of
+// four lanes, read where they are used, and no branch on a node: the conversions
+// of 24 nodes' values overlap. k_spread, 12,000 markers of a fish of 40 nodes in
+// 100x52x52: 28.1 us, 36.3 with a branch a node (28.7 with the values pinned
+// before it), 31.0 with four markers, 30.9 with one and the next one's loads
+// ahead; 36 when the records were staged in LDS, 256 at a time.
 constexpr int kHits = 1024;
 
 // w[q] becomes w[(q + r) & 3].

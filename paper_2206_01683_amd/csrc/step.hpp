@@ -33,9 +33,9 @@ namespace lbmib {
 // At most this many markers are interpolated straight from the populations (two
 // launches a step); more get the band macros first (three). The direct form saves
 // a launch and pulls 27 x 16 short rows for each marker, 55 KB of L2 lines. Us a
-// step from the macros and direct, F32: 500 markers on 64x32x32 20.2, 16.1, on
-// 192x96x96 80.8, 75.2; 2,000 on 64x32x32 25.7, 21.5, 128x64x64 33.8, 34.7,
-// 192x96x96 81.4, 80.2; 3,500 33.6, 32.1, then 36.2, 39.1 and 82.6, 83.7.
+// step from the macros and direct, F32, fish of 0.3 nx: 500 markers on 64x32x32
+// 23.0, 18.9, on 128x64x64 33.2, 32.6, on 192x96x96 80.1, 74.5; 2,000 34.0, 32.2,
+// then 34.8, 34.8 and 81.1, 79.4; 3,500 45.4, 45.6, then 36.8, 40.2 and 81.9, 82.4.
 constexpr int kDirectMarkers = 2000;
 // Sixteenths of the bulk in each launch before the last, enough to cover the
 // marker work there (2, 3 and 4 of them: fin 37.3, 37.2, 36.0 us, fish 539,
