@@ -823,7 +823,9 @@ __device__ inline void wrench_sum(const float *__restrict__ partials, int n, boo
 // of 24 nodes' values overlap. k_spread, 12,000 markers of a fish of 40 nodes in
 // 100x52x52: 28.1 us, 36.3 with a branch a node (28.7 with the values pinned
 // before it), 31.0 with four markers, 30.9 with one and the next one's loads
-// ahead; 36 when the records were staged in LDS, 256 at a time.
+// ahead; 36 when the records were staged in LDS, 256 at a time. The search
+// direction takes one marker, a component a lane (the 128x64x64 fin, k_spread_cg:
+// 8.4 us, 9.0 with two markers, 10.9 with all three components in each lane).
 constexpr int kHits = 1024;
 
 // w[q] becomes w[(q + r) & 3].
@@ -842,7 +844,7 @@ struct alignas(16) SpreadLds {
   int nhit;
 };
 
-__device__ inline void cg_direction(const EnvView &e, int k, const float *beta, bool first, float p[3]);
+__device__ inline float cg_direction(const EnvView &e, int k, int c, float beta, bool first);
 
 // Plane `plane` of tile t by the 256 threads tid = 0 .. 255 (each 256 threads
 // of a larger workgroup take a plane of the same tile). The record's values
@@ -850,7 +852,7 @@ __device__ inline void cg_direction(const EnvView &e, int k, const float *beta, 
 // the implicit correction's conjugate-gradient step (cg_direction with beta,
 // first). s.acc holds the start value (visible after the first barrier here);
 // a barrier ends the call.
-template <bool CG, int NC = 3, int FIRST = 16, int U = 2>
+template <bool CG, int NC = 3, int FIRST = 16, int U = CG ? 1 : 2>
 __device__ inline void spread_plane(const EnvView &e, const BodySet &bs, const TileAt &t, int plane, int tid,
                                     SpreadLds<NC> &s, const float *beta = nullptr, bool first = true) {
   const GridArgs &g = e.g;
@@ -858,6 +860,8 @@ __device__ inline void spread_plane(const EnvView &e, const BodySet &bs, const T
   const int n = e.n;
   const gmem<int> *list = (const gmem<int> *)e.list + t.off;
   constexpr int PER = kHits / 256, kMask = (1 << kListShift) - 1;
+  const int cc = min(lane & 3, 2);
+  const float bc = CG && !first ? beta[cc] : 0.f;
   for (int c0 = 0; c0 < t.cnt; c0 += kHits) {
     int entry[PER];
 #pragma unroll
@@ -885,16 +889,10 @@ __device__ inline void spread_plane(const EnvView &e, const BodySet &bs, const T
         ba[u] = *(const gmem<vfloat4> *)(rp + 12);
         fd[u] = *(const gmem<vfloat4> *)(rp + 16);
         wyz[u] = rp[4 + (lane & 3)] * rp[8 + (int)((unsigned)h >> kListShift)];
-        if (CG) {
-          float v[3];
-          cg_direction(e, k, beta, first, v);
-          if (e.slip) {  // the search direction is a normal force p n
-            const float p0 = v[0];
-            v[0] = p0 * bs.Nrm[k];
-            v[1] = p0 * bs.Nrm[n + k];
-            v[2] = p0 * bs.Nrm[2 * (size_t)n + k];
-          }
-          fd[u] = vfloat4{v[0], v[1], v[2], 0.f};
+        if (CG) {  // a component in each of the first three lanes of the four
+          float p = cg_direction(e, k, cc, bc, first);
+          if (e.slip) p = quad_lane<0>(p) * bs.Nrm[(size_t)cc * n + k];  // the search direction is a normal force p n
+          fd[u] = vfloat4{quad_lane<0>(p), quad_lane<1>(p), quad_lane<2>(p), 0.f};
         }
       }
 #pragma unroll
@@ -1086,17 +1084,13 @@ __device__ inline bool cg_last_arrival(int *counter, int count) {
   return last;
 }
 
-// Search direction of marker k: p = z + beta p_prev, z = 2 rho_k r (p = z on
-// the first step).
-__device__ inline void cg_direction(const EnvView &e, int k, const float *beta, bool first, float p[3]) {
+// Component c of the search direction of marker k: p = z + beta p_prev,
+// z = 2 rho_k r (p = z on the first step).
+__device__ inline float cg_direction(const EnvView &e, int k, int c, float beta, bool first) {
   const int n = e.n;
-  const float p2 = 2.0f * e.mstate[k];
   const float *r = e.cg + 3 * (size_t)n, *pp = e.cg + 6 * (size_t)n;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const float z = p2 * r[c * n + k];
-    p[c] = first ? z : z + beta[c] * pp[c * n + k];
-  }
+  const float z = 2.0f * e.mstate[k] * r[c * n + k];
+  return first ? z : z + beta * pp[c * n + k];
 }
 
 template <bool ROT>
@@ -1183,8 +1177,10 @@ __device__ inline void cg_apply_item(const EnvView &e, const BodySet &bs, int it
       q[0] = bs.Nrm[k] * qx + bs.Nrm[n + k] * qy + bs.Nrm[2 * (size_t)n + k] * qz;
       q[1] = q[2] = 0.f;
     }
+    const float *beta = cg_scal(e, 1, j);
     float p[3];
-    cg_direction(e, k, cg_scal(e, 1, j), j == 0, p);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) p[c] = cg_direction(e, k, c, j == 0 ? 0.f : beta[c], j == 0);
     float *qv = e.cg + 9 * (size_t)n, *pv = e.cg + 6 * (size_t)n;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
